@@ -68,9 +68,8 @@ typedef int rh_status;
 #define RH_KERNEL_SWEEP_Z 2   /* z-direction WENO sweep */
 #define RH_KERNEL_OTHER   3   /* combine, conversion, reduction and ideal-gas recovery kernels */
 #define RH_KERNEL_ADJOINT 4   /* adjoint sweeps (all axes) */
-#define RH_KERNEL_SWEEP_XY 5  /* fused x and y sweep (WENO5, and WENO7 in FP32; periodic x of
-                                 64..256 cells, a multiple of 64): one launch in place of the x
-                                 and y sweeps */
+#define RH_KERNEL_SWEEP_XY 5  /* fused x and y sweep (periodic x of 256 cells, and of 64, 128 or
+                                 192 for WENO5 in FP32): one launch in place of the x and y sweeps */
 #define RH_KERNEL_STAGE 6     /* fused stage: x, y and z of L and the stage combine in one launch */
 #define RH_KERNEL_CLASSES 7
 
@@ -81,8 +80,11 @@ typedef int rh_status;
  * axes of L and the stage combine (no L accumulator).  For the WENO schemes with
  * global splitting and the conformal fluid both give bitwise the same results;
  * MUSTA-FORCE, local splitting and the ideal gas exist on RH_PATH_STAGE only.
- * RH_PATH_AUTO (the default) takes RH_PATH_SWEEPS for single grids where it
- * applies and RH_PATH_STAGE otherwise and for batches. */
+ * RH_PATH_AUTO (the default) takes RH_PATH_STAGE for batches and where only it
+ * applies, and for other single grids the faster of the two: RH_PATH_STAGE for
+ * three-dimensional grids below a size that depends on scheme, precision and
+ * boundaries, RH_PATH_SWEEPS otherwise and while per-launch timing is on
+ * (rh_set_timing), so that the times are those of the directional sweeps. */
 #define RH_PATH_AUTO   0
 #define RH_PATH_SWEEPS 1
 #define RH_PATH_STAGE  2

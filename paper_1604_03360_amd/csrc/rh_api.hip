@@ -235,10 +235,43 @@ hipError_t launch_stage_of(const rh_grid_desc& d, int tx, bool hub, const rh::St
 // speed from a recovery pass run before it (MUSTA-FORCE recovers its own).
 bool needs_recovery(const rh_grid_desc& d) { return d.eos == RH_EOS_IDEAL && d.scheme != RH_SCHEME_MUSTA; }
 
+// Grids whose evaluations RH_PATH_AUTO gives to the fused stage (bitwise the
+// results of the sweeps).  One launch per stage instead of three, with as many
+// blocks as the chip takes, wins wherever latency or the L accumulator's traffic
+// counts: 31 against 135 us per FP32 WENO5 step at 33 x 20 x 17, 61 against 232 at
+// 64^3, 430 against 500 at 203 x 150 x 97, 1950 against 2240 at 256^3 with outflow
+// boundaries.  The sweeps are kept
+//   - for WENO5 where the fused x-y sweep applies to large grids (256^3 periodic:
+//     1855 against 1955 us FP32, 3675 against 3750 FP64; 128^3 FP32: 300 against 316;
+//     192 lanes per row leave it behind, 860 against 840),
+//   - for WENO7 from the size where the stage's fewer waves (two per SIMD in FP32,
+//     one in FP64) cost more than its traffic saves (FP32: 276 against 357 us at
+//     96^3, 521 against 515 at 128^3; FP64: 147 against 472 at 64^3, 506 against 477
+//     at 96^3, 8190 against 6600 at 256^3).
+bool auto_stage(const rh_grid_desc& d) {
+    if (d.nx < 2 || d.ny < 2 || d.nz < 2) return false;
+    const long long cells = (long long)d.nx * d.ny * d.nz;
+    const bool fp32 = d.precision == RH_PREC_FP32;
+    if (d.scheme == 7) return cells < (fp32 ? 2000000 : 500000);
+    const int n[3] = {d.nx, d.ny, d.nz};
+    const bool rows = d.nx % 128 == 0 && rh::sweep_xy_applies(5, fp32 ? 4 : 8, n, d.bc[0]);
+    return !(rows && cells >= 2000000);
+}
+
 // Path of a single grid's evaluations: the fused stage where it is requested
-// or where only it implements the scheme; RH_PATH_AUTO keeps the directional
-// sweeps otherwise.
-bool use_stage(const rh_plan* p) { return needs_stage(p->d) || p->path == RH_PATH_STAGE; }
+// or where only it implements the scheme, else RH_PATH_AUTO's choice.
+bool use_stage(const rh_plan* p) {
+    if (needs_stage(p->d) || p->path == RH_PATH_STAGE) return true;
+    return p->path == RH_PATH_AUTO && !p->timing && auto_stage(p->d);
+}
+
+// z segment of a plan's fused stage (set by the caller, or the default).
+int plan_stage_segment(const rh_plan* p) {
+    if (p->stage_seg > 0) return p->stage_seg;
+    const int n[3] = {p->d.nx, p->d.ny, p->d.nz};
+    if (p->d.scheme == RH_SCHEME_MUSTA) return rh::musta_default_segment(n);
+    return rh::stage_segment(1, &n, p->stage_tx, p->d.scheme, (int)p->elem, p->d.flux_split == RH_SPLIT_LOCAL);
+}
 
 // One evaluation of L at time t on `us`; stage == 0 stores L in `lacc`,
 // otherwise the stage combine writes `uout` from `us`, `u0` and dt.
@@ -277,11 +310,7 @@ rh_status evaluate(rh_plan* p, const T* us, const T* u0, T* lacc, T* uout, doubl
         sa.t = t;
         sa.clamps = p->d_clamps;
         sa.ngrid = 0;
-        const bool musta = p->d.scheme == RH_SCHEME_MUSTA;
-        fill_stage_grid<T>(sa.one, p->d, 0, p->stage_tx,
-                           p->stage_seg > 0 ? p->stage_seg
-                                            : (musta ? rh::musta_default_segment(n)
-                                                     : rh::stage_default_segment(n, p->stage_tx)));
+        fill_stage_grid<T>(sa.one, p->d, 0, p->stage_tx, plan_stage_segment(p));
         const long long nb = rh::stage_blocks(sa.one);
         if (needs_recovery(p->d)) {
             // the workspace's L slot is free on this path (the stage writes uout or lacc)
@@ -296,7 +325,7 @@ rh_status evaluate(rh_plan* p, const T* us, const T* u0, T* lacc, T* uout, doubl
         }, "stage launch");
     }
     int i0 = 0;
-    if (na >= 2 && active[0] == 0 && active[1] == 1 && rh::sweep_xy_applies(p->d.scheme, n, p->d.bc[0])) {
+    if (na >= 2 && active[0] == 0 && active[1] == 1 && rh::sweep_xy_applies(p->d.scheme, (int)sizeof(T), n, p->d.bc[0])) {
         // x and y in one launch
         rh::SweepArgs<T> b = a;
         b.first = 1;
@@ -644,11 +673,11 @@ rh_status rh_set_stage_tuning(rh_plan* p, int tile_x, int seg_z) {
 
 rh_status rh_get_stage_tuning(const rh_plan* p, int* tile_x, int* seg_z) {
     if (!p) return fail(RH_E_INVAL, "plan is NULL");
-    const int n[3] = {p->d.nx, p->d.ny, p->d.nz};
     if (tile_x) *tile_x = p->stage_tx;
-    if (seg_z) *seg_z = p->stage_seg > 0 ? (p->stage_seg < n[2] ? p->stage_seg : n[2])
-                                         : (p->d.scheme == RH_SCHEME_MUSTA ? rh::musta_default_segment(n)
-                                                                           : rh::stage_default_segment(n, p->stage_tx));
+    if (seg_z) {
+        const int seg = plan_stage_segment(p);
+        *seg_z = seg < p->d.nz ? seg : p->d.nz;
+    }
     return RH_OK;
 }
 
@@ -1075,6 +1104,16 @@ rh_status rh_batch_create(rh_batch** out, int n_grids, const rh_grid_desc* descs
             b->tile_x = tx;
         }
     }
+    if (b->scheme != RH_SCHEME_MUSTA) {
+        std::vector<int> n(3 * (size_t)n_grids);
+        for (int i = 0; i < n_grids; ++i) {
+            n[3 * i] = b->d[i].nx;
+            n[3 * i + 1] = b->d[i].ny;
+            n[3 * i + 2] = b->d[i].nz;
+        }
+        b->stage_seg = rh::stage_segment(n_grids, (const int (*)[3])n.data(), b->stage_tx, b->scheme, (int)b->elem,
+                                         b->d[0].flux_split == RH_SPLIT_LOCAL);
+    }
     hipError_t e;
     if ((e = hipMalloc(&b->d_clamps, sizeof(unsigned))) != hipSuccess ||
         (e = hipMalloc(&b->d_partials, 6 * rh::kTotalsBlocks * sizeof(double))) != hipSuccess ||
@@ -1391,7 +1430,7 @@ rh_status rh_batch_autotune(rh_batch* b, int reps) {
         rh_status rs = RH_OK;
         for (int tx : {16, 32}) {
             if (tx == 32 && b->scheme != 5) continue;
-            for (int sg : {16, 24, 32, 48, 64}) {
+            for (int sg : {4, 8, 16, 24, 32, 48, 64}) {
                 b->stage_tx = tx;
                 b->stage_seg = sg;
                 if ((rs = upload_table(b)) != RH_OK) break;

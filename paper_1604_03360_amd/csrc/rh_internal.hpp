@@ -133,9 +133,9 @@ int choose_tile_x(int nx, int ghosts);
 int choose_segment(int n, int ncols);
 
 // Fused x and y sweeps (one launch doing both axes, bitwise the result of the
-// x sweep followed by the y sweep): applies to WENO5 and WENO7 grids with a
-// periodic x axis of 64, 128, 192 or 256 cells and more than one cell along y.
-bool sweep_xy_applies(int order, const int n[3], int bc_x);
+// x sweep followed by the y sweep): applies to grids with a periodic x axis of
+// 256 cells (FP32 WENO5: 64, 128, 192 or 256) and more than one cell along y.
+bool sweep_xy_applies(int order, int elem, const int n[3], int bc_x);
 // a: the y sweep's arguments (first = 1; bc, inv_h of y); inv_hx = 1 / dx.
 template <class T>
 hipError_t launch_sweep_xy(int order, SweepArgs<T> a, T inv_hx, hipStream_t s);
@@ -205,8 +205,9 @@ long long stage_blocks(const StageGrid<T>& g) {
 template <class T>
 hipError_t launch_stage(int order, int tx, bool hub, bool local, int eos, const StageArgs<T>& a,
                         long long nblocks, hipStream_t s);
-// Default z segment of the fused stage for a grid of n cells (tiles of tx).
-int stage_default_segment(const int n[3], int tx);
+// z segment of the fused stage for a launch over ngrid grids of n[g] cells (tiles
+// of tx, elem bytes per value).
+int stage_segment(int ngrid, const int (*n)[3], int tx, int order, int elem, bool local);
 
 // MUSTA-FORCE stage (the same work items, with x-y tiles of kMustaTX x
 // kMustaTY cells): one launch evaluates the MUSCL + MUSTA face fluxes of x, y

@@ -776,14 +776,21 @@ __global__ void __launch_bounds__(256, (RollMinBlocks<T, ORDER>::value)) sweep_x
     if (clamped) atomicAdd(A.clamps, clamped);
 }
 
+// The LDS arrays are dimensioned for rows of 256 cells, so shorter rows leave
+// part of it idle.  FP32 WENO5 blocks are small enough to fit several per CU all
+// the same (128^3: 300 against 336 us per step for the separate sweeps); in FP64
+// and for WENO7 only full rows win (per step, fused against separate: FP64 WENO5 668 and 552 us at
+// 128^3, 3670 and 4265 at 256^3; FP32 WENO7 1600 and 1535 at 192^3; FP64 WENO7
+// 3520 and 2945 at 192^3).
 // RH_FUSE_XY=0 in the environment selects the separate sweeps everywhere (the
 // results are bitwise the same; used to compare the two paths).
-bool sweep_xy_applies(int order, const int n[3], int bc_x) {
+bool sweep_xy_applies(int order, int elem, const int n[3], int bc_x) {
     static const bool off = [] {
         const char* e = getenv("RH_FUSE_XY");
         return e && e[0] == '0';
     }();
-    return !off && (order == 5 || order == 7) && bc_x == RH_BC_PERIODIC && n[0] % 64 == 0 &&
+    const int step = order == 5 && elem == 4 ? 64 : 256;
+    return !off && (order == 5 || order == 7) && bc_x == RH_BC_PERIODIC && n[0] % step == 0 &&
            n[0] >= 64 && n[0] <= 256 && n[1] > 1;
 }
 

@@ -6,13 +6,22 @@
 // in memory.  A work item is (grid, x-y tile of TX x TY = 256 cells, z segment):
 // the block rolls along its z segment one plane at a time.  Each lane owns one
 // (x, y) column of the tile and keeps a register window of 2R doubled split
-// fluxes along z (as the rolling sweeps do); for every owned plane the block
-// stages the tile's doubled x and y split fluxes in LDS, with R halo cells on
-// each side along x and along y (no corners are needed), reconstructs every x
-// and y face of the tile once and keeps the x + y part of L for R planes until
-// the z face above the cell is known.  Every cell of the tile is loaded and
-// recovered (FP64) once per plane; the halo cells of the tile are recovered
-// again by the tiles that own them.
+// fluxes along z (as the rolling sweeps do), R planes ahead of the plane that is
+// finished.  For that plane the block stages the tile's doubled x and y split
+// fluxes in LDS, with R halo cells on each side along x and along y (no corners
+// are needed), and reconstructs every x and y face of the tile once; the z faces
+// come from the window, so the plane is complete and stored at once.  A cell of
+// the tile is loaded and recovered (FP64) twice, when it enters the z window and
+// when its own plane is staged.  The second recovery costs about 50 of 1300
+// instructions per cell; keeping the x + y part of L for R planes instead (one
+// recovery, a register ring, the stage input loaded again for the combine) took
+// 15 more registers and a fill of 2R dependent planes, and measured 2.18 against
+// 1.94 ms per FP32 WENO5 step and 3.98 against 3.63 ms in FP64 at 256^3, and 34.6
+// against 30.0 us at 16^3.  The window's 2R planes are loaded before the first
+// is recovered, so that a segment of one plane waits for memory once.  What bounds
+// it: VALU issue where the chip is full (FP32: three waves per SIMD, 156
+// registers; capped at 128 registers for a fourth, the spills cost 14%); the dependent chains of
+// recovery and reconstruction of one plane (about 5 us) where it is not.
 //
 // The arithmetic of every face, flux difference and combine is that of the
 // split sweeps, summed in the same order (x, then y, then z), so the result is
@@ -58,7 +67,7 @@ __device__ __forceinline__ T stage_recon_minus(const T* w, T eps2) {
 // half of the 160 KB LDS.
 template <class T, int ORDER, int TX, bool LOCAL>
 struct StageMinBlocks {
-    static constexpr int value = sizeof(T) == 4 ? 3 : (ORDER == 5 && TX == 16 && !LOCAL ? 2 : 1);
+    static constexpr int value = sizeof(T) == 4 ? (ORDER == 5 && !LOCAL ? 3 : 2) : (ORDER == 5 && TX == 16 && !LOCAL ? 2 : 1);
 };
 
 // One face from the staged pairs of its 2R stencil cells: global splitting
@@ -152,14 +161,14 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
         hyc = y0 - R + hr;
     }
 
-    auto fetch_own = [&](int m, T u[5]) {
-        if (m >= 0 && m < nz) {
-            const uint32_t off = cb + (uint32_t)m * sb;
+    auto fetch_plane = [&](int k, T u[5]) {   // own cell of a plane of the grid
+        const uint32_t off = cb + (uint32_t)k * sb;
 #pragma unroll
-            for (int f = 0; f < 5; ++f) u[f] = ld_off(us + f * F, off);
-        } else {
-            stage_load<T, HUB>(G, us, F, t, cx, cy, m, u);
-        }
+        for (int f = 0; f < 5; ++f) u[f] = ld_off(us + f * F, off);
+    };
+    auto fetch_own = [&](int m, T u[5]) {     // the same, or a ghost plane's
+        if (m >= 0 && m < nz) fetch_plane(m, u);
+        else stage_load<T, HUB>(G, us, F, t, cx, cy, m, u);
     };
     auto fetch_halo = [&](int m, T u[5]) {
         if (hkind) stage_load<T, HUB>(G, us, F, t, hxc, hyc, m, u);
@@ -181,73 +190,74 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
 
     T zp[5][W], zm[5][W];     // z window: staged pairs of cells k - R .. k + R - 1
     T zsp[LOCAL ? W : 1];     // LOCAL: their largest speeds along z
-    T ring[R][5];             // x + y part of L of the last R owned planes, oldest first
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-#pragma unroll
-        for (int j = 0; j < W; ++j) zp[c][j] = zm[c][j] = (T)0;
-#pragma unroll
-        for (int j = 0; j < R; ++j) ring[j][c] = (T)0;
-    }
-#pragma unroll
-    for (int j = 0; j < (LOCAL ? W : 1); ++j) zsp[j] = (T)0;
 
-    // Enter plane m: recover the own cell, shift its z split fluxes into the
-    // window and, for an owned plane, stage the x / y split fluxes of the own
-    // and halo cells.
-    auto enter = [&](int m, const T u[5], const T hu[5], bool owned) {
-        // velocity, pressure (and, for the local splitting, v^2 and c_s^2) of the
-        // own cell: FP64 closed-form recovery, or read from the recovery pass
-        // (loaded here, not a plane ahead: the registers of a prefetch spill)
-        T VX, VY, VZ, P;
-        double vxd, vyd, vzd, v2 = 0.0, cs2 = 0.0;
-        unsigned c0 = 0;
+    // z pair of a cell entering the window (and its largest speed along z)
+    auto z_pair = [&](int m, const T u[5], T fp[5], T fm[5], T& speed) {
+        T VZ, P;
         if constexpr (EOS == EOS_IDEAL) {
-            T pu[5];
-            fetch_own_prim(m, pu);
-            VX = pu[0];
-            VY = pu[1];
-            VZ = pu[2];
-            P = pu[3];
-            vxd = (double)VX;
-            vyd = (double)VY;
-            vzd = (double)VZ;
+            T q[5];
+            fetch_own_prim(m, q);
+            VZ = q[2];
+            P = q[3];
             if constexpr (LOCAL) {
-                v2 = vxd * vxd + vyd * vyd + vzd * vzd;
-                cs2 = (double)pu[4];
+                const double vx = (double)q[0], vy = (double)q[1], vz = (double)VZ;
+                speed = (T)max_char_speed(vz, vx * vx + vy * vy + vz * vz, (double)q[4]);
             }
         } else {
-            double kap, Mxs, Mys, Mzs, p;
-            recover_kp3((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, Mzs, p, c0);
-            vxd = kap * Mxs;
-            vyd = kap * Mys;
-            vzd = kap * Mzs;
-            VX = (T)vxd;
-            VY = (T)vyd;
-            VZ = (T)vzd;
-            P = (T)p;
-            cs2 = 1.0 / 3.0;
-            if constexpr (LOCAL) v2 = kap * kap * (Mxs * Mxs + Mys * Mys + Mzs * Mzs);
-        }
-        T fp[5], fm[5];
-        stage_pair<T, 2, LOCAL>(u, VZ, P, fp, fm);
-#pragma unroll
-        for (int c = 0; c < 5; ++c) {
-#pragma unroll
-            for (int j = 0; j < W - 1; ++j) {
-                zp[c][j] = zp[c][j + 1];
-                zm[c][j] = zm[c][j + 1];
+            unsigned dummy = 0;   // floors are counted when the cell's own plane is staged
+            if constexpr (LOCAL) {
+                double kap, Mxs, Mys, Mzs, p;
+                recover_kp3((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, Mzs, p, dummy);
+                VZ = (T)(kap * Mzs);
+                P = (T)p;
+                speed = (T)max_char_speed(kap * Mzs, kap * kap * (Mxs * Mxs + Mys * Mys + Mzs * Mzs), 1.0 / 3.0);
+            } else {
+                double vd, p;
+                recover_vp<2>((double)u[0], (double)u[1], (double)u[2], (double)u[3], vd, p, dummy);
+                VZ = (T)vd;
+                P = (T)p;
             }
-            zp[c][W - 1] = fp[c];
-            zm[c][W - 1] = fm[c];
         }
-        if constexpr (LOCAL) {
-#pragma unroll
-            for (int j = 0; j < W - 1; ++j) zsp[j] = zsp[j + 1];
-            zsp[W - 1] = (T)max_char_speed(vzd, v2, cs2);
-        }
-        if (!owned) return;
+        stage_pair<T, 2, LOCAL>(u, VZ, P, fp, fm);
+    };
+
+    // Stage the x and y pairs of the own cell of plane k and of the lane's halo
+    // cell in LDS.
+    auto stage_xy = [&](int k, const T u[5], const T hu[5]) {
+        T fp[5], fm[5];
         if (act) {
+            T VX, VY, P;
+            double vxd, vyd, v2 = 0.0, cs2 = 0.0;
+            unsigned c0 = 0;
+            if constexpr (EOS == EOS_IDEAL) {
+                T q[5];
+                fetch_own_prim(k, q);
+                VX = q[0];
+                VY = q[1];
+                P = q[3];
+                vxd = (double)VX;
+                vyd = (double)VY;
+                if constexpr (LOCAL) {
+                    const double vzd = (double)q[2];
+                    v2 = vxd * vxd + vyd * vyd + vzd * vzd;
+                    cs2 = (double)q[4];
+                }
+            } else {
+                double kap, Mxs, Mys, p;
+                if constexpr (!LOCAL) {
+                    recover_kp((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, p, c0);
+                } else {
+                    double Mzs;
+                    recover_kp3((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, Mzs, p, c0);
+                    v2 = kap * kap * (Mxs * Mxs + Mys * Mys + Mzs * Mzs);
+                    cs2 = 1.0 / 3.0;
+                }
+                vxd = kap * Mxs;
+                vyd = kap * Mys;
+                VX = (T)vxd;
+                VY = (T)vyd;
+                P = (T)p;
+            }
             clamped += c0;   // floors counted once per owned cell and evaluation of L
             stage_pair<T, 0, LOCAL>(u, VX, P, fp, fm);
 #pragma unroll
@@ -271,7 +281,7 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
             double hxd, hyd, hv2 = 0.0, hcs2 = 0.0;
             if constexpr (EOS == EOS_IDEAL) {
                 T phu[5];
-                fetch_halo_prim(m, phu);
+                fetch_halo_prim(k, phu);
                 HX = phu[0];
                 HY = phu[1];
                 HP = phu[3];
@@ -320,9 +330,8 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
         }
     };
 
-    // x + y part of L of the staged (owned) plane, pushed into the ring
-    auto plane_xy = [&]() {
-        __syncthreads();
+    // x and y faces of the staged plane
+    auto faces_xy = [&]() {
         if (act) {
             T ax = (T)0, ay = (T)0;
             if constexpr (LOCAL) {
@@ -332,9 +341,7 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
                     ay = max(ay, ssy[ly + 1 + j][lx]);
                 }
             }
-            // one component at a time: unrolled, the LDS reads of all five
-            // windows would be hoisted and raise the register peak
-#pragma unroll 1
+#pragma unroll
             for (int c = 0; c < 5; ++c) {
                 // window of face x + 1/2: staged columns lx + 1 .. lx + 2R
                 if constexpr (LOCAL) {
@@ -393,23 +400,6 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
                 fy[c][0][col] = stage_recon_plus<T, ORDER>(wp, eps2) + stage_recon_minus<T, ORDER>(wm, eps2);
             }
         }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < R - 1; ++j)
-#pragma unroll
-            for (int c = 0; c < 5; ++c) ring[j][c] = ring[j + 1][c];
-#pragma unroll
-        for (int c = 0; c < 5; ++c) {
-            const T Lx = dox ? (fx[c][ly][lx] - fx[c][ly][lx + 1]) * hxinv : (T)0;
-            const T Ly = doy ? (fy[c][ly][lx] - fy[c][ly + 1][lx]) * hyinv : (T)0;
-            ring[R - 1][c] = Lx + Ly;
-        }
-    };
-    auto push_none = [&]() {
-#pragma unroll
-        for (int j = 0; j < R - 1; ++j)
-#pragma unroll
-            for (int c = 0; c < 5; ++c) ring[j][c] = ring[j + 1][c];
     };
     // z face above the window's centre, component c
     auto zface = [&](int c) {
@@ -423,70 +413,107 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
         }
     };
 
-    // fill: planes k0 - R .. k0 + R - 1 (the z window of face k0 - 1/2)
-    T nu[5], nh[5] = {(T)0, (T)0, (T)0, (T)0, (T)0};
-    fetch_own(k0 - R, nu);
-    for (int m = k0 - R; m < k0 + R; ++m) {
-        T u[5], hu[5];
+    // z window of face k0 - 1/2: planes k0 - R .. k0 + R - 1, all loads issued
+    // before the first recovery (a block of few planes waits once, not 2R times)
+    {
+        T fu[W][5];
 #pragma unroll
-        for (int f = 0; f < 5; ++f) {
-            u[f] = nu[f];
-            hu[f] = nh[f];
+        for (int j = 0; j < W; ++j) fetch_own(k0 - R + j, fu[j]);
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            T fp[5], fm[5], sz = (T)0;
+            z_pair(k0 - R + j, fu[j], fp, fm, sz);
+#pragma unroll
+            for (int c = 0; c < 5; ++c) {
+                zp[c][j] = fp[c];
+                zm[c][j] = fm[c];
+            }
+            if constexpr (LOCAL) zsp[j] = sz;
         }
-        const bool owned = m >= k0 && m < kend;
-        fetch_own(m + 1, nu);
-        if (m + 1 >= k0 && m + 1 < kend) fetch_halo(m + 1, nh);
-        enter(m, u, hu, owned);
-        if (owned) plane_xy();
-        else if (m >= k0) push_none();
+    }
+    // operands of the next plane, in flight during this one; with analytic ghost
+    // cells the window's next plane only (all three spill: 128^3 FP64 551 us per
+    // step against 531, FP32 368 against 350)
+    constexpr bool AHEAD = !HUB;
+    T nz5[5], no5[5], nh5[5] = {(T)0, (T)0, (T)0, (T)0, (T)0};
+    fetch_own(k0 + R, nz5);
+    if constexpr (AHEAD) {
+        fetch_plane(k0, no5);
+        fetch_halo(k0, nh5);
     }
     T Fl[5];
 #pragma unroll
     for (int c = 0; c < 5; ++c) Fl[c] = zface(c);
 
-    // main loop: plane m = k + R enters, cell k is finished
     for (int k = k0; k < kend; ++k) {
-        const int m = k + R;
-        T u[5], hu[5];
+        T uz[5], u[5];
+        if constexpr (!AHEAD) {
+            fetch_plane(k, no5);
+            fetch_halo(k, nh5);
+        }
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
-            u[f] = nu[f];
-            hu[f] = nh[f];
+            uz[f] = nz5[f];
+            u[f] = no5[f];
         }
-        const bool owned = m < kend;
-        if (k + 1 < kend) fetch_own(m + 1, nu);
-        if (m + 1 < kend) fetch_halo(m + 1, nh);
-        const uint32_t off = cb + (uint32_t)k * sb;
-        enter(m, u, hu, owned);
-        T Lk[5];
+        stage_xy(k, u, nh5);
+        if (k + 1 < kend) {
+            fetch_own(k + 1 + R, nz5);
+            if constexpr (AHEAD) {
+                fetch_plane(k + 1, no5);
+                fetch_halo(k + 1, nh5);
+            }
+        }
+        {
+            T fp[5], fm[5], sz = (T)0;
+            z_pair(k + R, uz, fp, fm, sz);
+#pragma unroll
+            for (int c = 0; c < 5; ++c) {
+#pragma unroll
+                for (int j = 0; j < W - 1; ++j) {
+                    zp[c][j] = zp[c][j + 1];
+                    zm[c][j] = zm[c][j + 1];
+                }
+                zp[c][W - 1] = fp[c];
+                zm[c][W - 1] = fm[c];
+            }
+            if constexpr (LOCAL) {
+#pragma unroll
+                for (int j = 0; j < W - 1; ++j) zsp[j] = zsp[j + 1];
+                zsp[W - 1] = sz;
+            }
+        }
+        T Lz[5];
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
             // the z face is reconstructed for every grid (on ghost copies where nz is
             // 1) and discarded by a select, which keeps it out of a branch
             const T Fr = zface(c);
-            const T Lz = doz ? (Fl[c] - Fr) * hzinv : (T)0;
+            Lz[c] = doz ? (Fl[c] - Fr) * hzinv : (T)0;
             Fl[c] = Fr;
-            Lk[c] = ring[0][c] + Lz;
         }
-        // the stage input and u^n of cell k, loaded after the reconstructions
-        // to keep them out of the register peak
+        const uint32_t off = cb + (uint32_t)k * sb;
+        T u0k[5];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) u0k[c] = A.stage >= STAGE_2 ? ld_off(u0 + c * F, off) : (T)0;
+        __syncthreads();
+        faces_xy();
+        __syncthreads();
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
-            const T L = Lk[c];
-            const T usk = A.stage != STAGE_WRITE_L ? ld_off(us + c * F, off) : (T)0;
-            const T u0k = A.stage >= STAGE_2 ? ld_off(u0 + c * F, off) : (T)0;
+            const T Lx = dox ? (fx[c][ly][lx] - fx[c][ly][lx + 1]) * hxinv : (T)0;
+            const T Ly = doy ? (fy[c][ly][lx] - fy[c][ly + 1][lx]) * hyinv : (T)0;
+            const T L = (Lx + Ly) + Lz[c];
             T v;
             if (A.stage == STAGE_WRITE_L) {
                 v = L;
             } else {
-                v = usk + A.dt * L;
-                if (A.stage == STAGE_2) v = (T)0.75 * u0k + (T)0.25 * v;
-                else if (A.stage == STAGE_3) v = rk3_last(u0k, v);
+                v = u[c] + A.dt * L;
+                if (A.stage == STAGE_2) v = (T)0.75 * u0k[c] + (T)0.25 * v;
+                else if (A.stage == STAGE_3) v = rk3_last(u0k[c], v);
             }
             if (act) st_off(out + c * F, off, v);
         }
-        if (owned) plane_xy();
-        else push_none();
     }
     if (clamped) atomicAdd(A.clamps, clamped);
 }
@@ -539,20 +566,40 @@ template hipError_t launch_recover_ideal<double>(const StageArgs<double>&, long 
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-int stage_default_segment(const int n[3], int tx) {
-    // enough blocks to fill the chip several times over (about 3 x 256 x 4
-    // resident blocks), segments of 16 to 64 planes (each segment re-enters
-    // 2R halo planes)
+// z segment of the fused stage for the grids of a launch: the length with the
+// least estimated time, in units of one plane of a block that has its CU to
+// itself.  Such a block takes 1 + seg (the window fill costs about one plane);
+// with every resident slot of a CU taken, a block costs q (0.6 + seg).  Fitted
+// to 16^3 .. 256^3 at seg 1 .. 64 (FP32 WENO5: 10.0 us at seg 1 and 86 us at seg
+// 16 alone, 3.9 and 40 us per block with the chip full); the choices are within
+// 5% of the best measured segment.  Small grids get segments of one plane (16^3
+// FP32: 30 us per step, 258 us with one segment of 16), 256^3 gets 16 to 32.
+int stage_segment(int ngrid, const int (*n)[3], int tx, int order, int elem, bool local) {
     const int ty = 256 / tx;
-    const long long tiles = (long long)((n[0] + tx - 1) / tx) * ((n[1] + ty - 1) / ty);
-    const long long target = 4096;
-    long long nseg = (target + tiles - 1) / tiles;
-    const long long max_seg = (n[2] + 15) / 16;
-    if (nseg > max_seg) nseg = max_seg;
-    if (nseg < 1) nseg = 1;
-    int seg = (int)((n[2] + nseg - 1) / nseg);
-    if (seg > 64) seg = 64;
-    return seg;
+    const bool light = order == 5 && !local;
+    const int occ = elem == 4 ? (light ? 3 : 2) : (light && tx == 16 ? 2 : 1);
+    const double q = elem == 4 ? (light ? 0.46 : 0.62) : (light ? 0.74 : 1.05);
+    int best = 1;
+    double best_t = 1e300;
+    for (int seg : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
+        long long blocks = 0;
+        int planes = 1;
+        for (int g = 0; g < ngrid; ++g) {
+            const int nseg = (n[g][2] + seg - 1) / seg;
+            blocks += (long long)((n[g][0] + tx - 1) / tx) * ((n[g][1] + ty - 1) / ty) * nseg;
+            if (n[g][2] > planes) planes = n[g][2];
+        }
+        const double alone = 1.0 + (seg < planes ? seg : planes), full = q * (0.6 + seg);
+        const long long per_cu = (blocks + 255) / 256;
+        const double round = occ * full > alone ? occ * full : alone;
+        const double rest = (per_cu % occ) * full;
+        const double t = (per_cu / occ) * round + (per_cu % occ ? (rest > alone ? rest : alone) : 0.0);
+        if (t < best_t * (1.0 - 1e-9)) {
+            best_t = t;
+            best = seg;
+        }
+    }
+    return best;
 }
 
 template <class T>
