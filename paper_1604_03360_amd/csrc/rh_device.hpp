@@ -32,32 +32,32 @@ template <class T>
 __device__ __forceinline__ T rk3_last(T un, T v) { return un + (T)(2.0 / 3.0) * (v - un); }
 
 // Reciprocals.  FP32: the hardware reciprocal (about 1 ulp).  FP64: the
-// hardware estimate refined by two Newton-Raphson steps r <- r + r (1 - x r),
-// which carries the estimate to full double precision for the normal-range
-// arguments used here (weight sums, (2E + D)(E + D)).
+// hardware estimate (measured within 2^-24.4) with one third-order step,
+// e = 1 - x r, r (1 + e + e^2), for the normal-range arguments used here (weight
+// sums, (2E + D)(E + D)).  Over 4e6 arguments of 1e-24 .. 1e24 its error is that
+// of two Newton steps (largest 1.11e-16, rms 4.9e-17 relative), one operation
+// less.
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double fast_rcp(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 
 // Square root of a positive normal double (no rescaling of tiny or huge
-// arguments, no special cases): the hardware reciprocal square root y refined
-// by one coupled Goldschmidt step on (g, h) ~ (sqrt(x), 1/(2 sqrt(x))) and two
-// Newton corrections g <- g + (x - g^2) h.  Used for 4E^2 - 3M^2 >= E^2 with E
-// above the floor, which is always in the normal range.
+// arguments, no special cases): the hardware reciprocal square root y (measured
+// within 2^-24.2) refined by one coupled Goldschmidt step on (g, h) ~ (sqrt(x),
+// 1/(2 sqrt(x))) and one Newton correction g <- g + (x - g^2) h.  Over 4e6
+// arguments the error is within 1.11e-16, rms 4.6e-17 relative, as with a second
+// correction.  Used for 4E^2 - 3M^2 >= E^2 with E above the floor, which is
+// always in the normal range.
 __device__ __forceinline__ double sqrt_pos(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     double g = x * y, h = 0.5 * y;
     const double r = fma(-g, h, 0.5);
     g = fma(g, r, g);
     h = fma(h, r, h);
-    double d = fma(-g, g, x);
-    g = fma(d, h, g);
-    d = fma(-g, g, x);
+    const double d = fma(-g, g, x);
     return fma(d, h, g);
 }
 
