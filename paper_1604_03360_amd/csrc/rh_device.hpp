@@ -323,11 +323,13 @@ __device__ __forceinline__ void split_flux(const T u[5], T fp[5], T fm[5], unsig
 //   q_k - c:  (-E1/3 + 5 E2/6), (E2/6 + E3/3), (2 E3/3 - E4/6)
 //   beta_k = 13/12 A_k^2 + 1/4 B_k^2 with A = (E2-E1, E3-E2, E4-E3),
 //            B = (3E2-E1, E2+E3, E4-3E3).
-// Expanded in the E's, 4 beta_k = 16/3 h_k with
-//   h0 = E1^2 - 11/4 E1 E2 + 5/2 E2^2,  h1 = E2^2 - 5/4 E2 E3 + E3^2,
-//   h2 = E4^2 - 11/4 E3 E4 + 5/2 E3^2
-// (positive definite), so g_k = (h_k + 3/16 (4 eps))^2 is (3/16)^2 (4 eps +
-// 4 beta_k)^2 and the common factor cancels in the weights
+// Completing the square in the outer difference, 4 beta_k = 16/3 h_k with
+//   h0 = (E1 - 11/8 E2)^2 + c E2^2,  h1 = (E2 - 5/8 E3)^2 + c E3^2,
+//   h2 = (E4 - 11/8 E3)^2 + c E3^2,  c = 39/64
+// (the remainder is the least energy given the difference that two
+// neighbouring candidates share, so h1 and h2 have it in common, and c is the same for all), so
+// g_k = (h_k + 3/16 (4 eps))^2 is (3/16)^2 (4 eps + 4 beta_k)^2 and the common
+// factor cancels in the weights
 // alpha_k = d_k / (eps + beta_k)^2, d = (1, 6, 3)/10, which are evaluated with
 // one reciprocal and carried as 10 w = (g1 g2, 6 g0 g2, 3 g0 g1), the factors 6
 // and 3 folded into the candidates of the numerator:
@@ -339,9 +341,11 @@ __device__ __forceinline__ T weno5(T s0, T s1, T s2, T s3, T s4, T eps4) {
     const T dq1s = E2 + (T)2 * E3;                              // 6 (q1 - c)
     const T dq2s = (T)2 * E3 - (T)0.5 * E4;                     // 3 (q2 - c)
     const T e = (T)0.1875 * eps4;
-    T g0 = E1 * (E1 - (T)2.75 * E2) + ((T)2.5 * E2 * E2 + e);
-    T g1 = E2 * (E2 - (T)1.25 * E3) + (E3 * E3 + e);
-    T g2 = E4 * (E4 - (T)2.75 * E3) + ((T)2.5 * E3 * E3 + e);
+    const T p2 = ((T)0.609375 * E2) * E2 + e, p3 = ((T)0.609375 * E3) * E3 + e;
+    const T a0 = E1 - (T)1.375 * E2, a1 = E2 - (T)0.625 * E3, a2 = E4 - (T)1.375 * E3;
+    T g0 = a0 * a0 + p2;
+    T g1 = a1 * a1 + p3;
+    T g2 = a2 * a2 + p3;
     g0 *= g0;
     g1 *= g1;
     g2 *= g2;
