@@ -355,80 +355,69 @@ __device__ __forceinline__ T weno5(T s0, T s1, T s2, T s3, T s4, T eps4) {
     return s2 + num * fast_rcp(den);
 }
 
-// WENO7: s0..s6 = f_{i-3..i+3}; linear weights (1, 12, 18, 4)/35.  With
-// D_j = s_j - s_{j-1} and c = s3, the candidates are c + dq_k and the cubic
-// candidate p_k = a0 + a1 x + a2 x^2 + a3 x^3 gives
-// beta_k = a1^2 + a1 a3 / 2 + 13/3 a2^2 + 3129/80 a3^2 (the sum of the cell
-// integrals of its squared first three derivatives).  a2 and a3 are carried
-// pre-scaled by sqrt(13/3) and sqrt(3129/80).
+// Smoothness of the four WENO7 candidates in the differences D1..D6 of the
+// stencil.  beta_k is the sum of the cell integrals of the squared first three
+// derivatives of the cubic on its four cells, a quadratic form in its three
+// differences.  Completing the square in the outermost one leaves the least value over the
+// cubics through the other three cells, which two neighbouring candidates share:
+//   240/547 beta_0 = l0^2 + q(D3, D2),  240/547 beta_1 = l1^2 + q(D3, D2),
+//   240/547 beta_2 = l2^2 + q(D4, D5),  240/547 beta_3 = l3^2 + q(D4, D5),
+//   l0 = D1 + (927 D3 - 1394 D2)/547,  l1 = D4 + (247 D2 - 714 D3)/547 and
+//   mirrored, q(a, b) = c2 (b - r a)^2 + c3 a^2, r = 3167/2126,
+//   c2 = 1063/1641 * 240/547, c3 = 10153/12756 * 240/547.
+// The factor 240/547 (on eps too) cancels in the weights.  22 operations for all
+// four, no cancellation; the derivative coefficients squared took 46 and the
+// expanded forms 36.
+template <class T>
+struct Smooth7 {
+    T l0, l1, l2, l3;   // the completed squares
+    T m1, m2;           // D2 - r D3 and D5 - r D4
+    T g0, g1, g2, g3;   // 240/547 (beta_k + eps)
+};
+template <class T>
+__device__ __forceinline__ Smooth7<T> smooth7(T D1, T D2, T D3, T D4, T D5, T D6, T eps) {
+    constexpr double f = 240.0 / 547.0, r = 3167.0 / 2126.0;
+    constexpr double c2 = 1063.0 / 1641.0 * f, c3 = 10153.0 / 12756.0 * f;
+    const T e = (T)f * eps;
+    Smooth7<T> o;
+    o.m1 = D2 - (T)r * D3;
+    o.m2 = D5 - (T)r * D4;
+    const T q1 = ((T)c2 * o.m1) * o.m1 + (((T)c3 * D3) * D3 + e);
+    const T q2 = ((T)c2 * o.m2) * o.m2 + (((T)c3 * D4) * D4 + e);
+    o.l0 = (D1 + (T)(927.0 / 547.0) * D3) - (T)(1394.0 / 547.0) * D2;
+    o.l1 = (D4 + (T)(247.0 / 547.0) * D2) - (T)(714.0 / 547.0) * D3;
+    o.l2 = (D3 + (T)(247.0 / 547.0) * D5) - (T)(714.0 / 547.0) * D4;
+    o.l3 = (D6 + (T)(927.0 / 547.0) * D4) - (T)(1394.0 / 547.0) * D5;
+    o.g0 = o.l0 * o.l0 + q1;
+    o.g1 = o.l1 * o.l1 + q1;
+    o.g2 = o.l2 * o.l2 + q2;
+    o.g3 = o.l3 * o.l3 + q2;
+    return o;
+}
+
+// WENO7: s0..s6 = f_{i-3..i+3}; linear weights d = (1, 12, 18, 4)/35.  With
+// D_j = s_j - s_{j-1} and c = s3, the candidates are c + dq_k; 35 d is folded
+// into the candidates, q_k = 35 d_k dq_k, and the weight sum.
 template <class T>
 __device__ __forceinline__ T weno7(T s0, T s1, T s2, T s3, T s4, T s5, T s6, T eps) {
     const T D1 = s1 - s0, D2 = s2 - s1, D3 = s3 - s2, D4 = s4 - s3, D5 = s5 - s4, D6 = s6 - s5;
-    const T dq0 = (T)0.25 * D1 - (T)(5.0 / 6.0) * D2 + (T)(13.0 / 12.0) * D3;
-    const T dq1 = (T)(1.0 / 3.0) * D3 - (T)(1.0 / 12.0) * D2 + (T)0.25 * D4;
-    const T dq2 = (T)(1.0 / 12.0) * (D3 - D5) + (T)0.5 * D4;
-    const T dq3 = (T)0.75 * D4 - (T)(1.0 / 3.0) * D5 + (T)(1.0 / 12.0) * D6;
-    const T r2 = (T)2.0816659994661326;    // sqrt(13/3)
-    const T kk = (T)(0.5 / 6.253998720818545);   // 1 / (2 sqrt(3129/80))
-    const T a1_0 = (T)(7.0 / 24.0) * D1 - (T)(13.0 / 12.0) * D2 + (T)(43.0 / 24.0) * D3;
-    const T a1_1 = (T)(11.0 / 12.0) * D3 - (T)(5.0 / 24.0) * D2 + (T)(7.0 / 24.0) * D4;
-    const T a1_2 = (T)(7.0 / 24.0) * D3 + (T)(11.0 / 12.0) * D4 - (T)(5.0 / 24.0) * D5;
-    const T a1_3 = (T)(43.0 / 24.0) * D4 - (T)(13.0 / 12.0) * D5 + (T)(7.0 / 24.0) * D6;
-    const T a2_0 = (T)(0.5 * 2.0816659994661326) * D1 - (T)(1.5 * 2.0816659994661326) * D2 + r2 * D3;
-    const T a2_1 = (T)(0.5 * 2.0816659994661326) * (D4 - D3);
-    const T a2_3 = (T)(1.5 * 2.0816659994661326) * D5 - r2 * D4 - (T)(0.5 * 2.0816659994661326) * D6;
-    const T c6 = (T)(6.253998720818545 / 6.0);
-    const T a3_0 = c6 * ((D1 + D3) - (T)2 * D2);
-    const T a3_1 = c6 * ((D2 + D4) - (T)2 * D3);
-    const T a3_2 = c6 * ((D3 + D5) - (T)2 * D4);
-    const T a3_3 = c6 * ((D4 + D6) - (T)2 * D5);
-    T g0, g1, g2, g3;
-    if constexpr (sizeof(T) == 4) {
-        // FP32: 240 beta_k as quadratic forms in its three differences
-        // (x, y, z) = (D_{k+1}, D_{k+2}, D_{k+3}); the factor 240 (on eps too)
-        // cancels in the weights.  Fewer operations than the derivative form.
-        // Rounding in the terms grows by at most the ratio of the summed
-        // absolute coefficients to 240 (68 for the outer stencils): a few 1e-6
-        // relative in beta at FP32, far below the parity bar.
-        const T e = (T)240 * eps;
-        auto q = [e](T x, T y, T z, T cxx, T cxy, T cxz, T cyy, T cyz, T czz) {
-            return x * (cxx * x + cxy * y + cxz * z) + (y * (cyy * y + cyz * z) + (czz * z * z + e));
-        };
-        g0 = q(D1, D2, D3, (T)547, (T)-2788, (T)1854, (T)3708, (T)-5188, (T)2107);
-        g1 = q(D2, D3, D4, (T)267, (T)-1108, (T)494, (T)1468, (T)-1428, (T)547);
-        g2 = q(D3, D4, D5, (T)547, (T)-1428, (T)494, (T)1468, (T)-1108, (T)267);
-        g3 = q(D4, D5, D6, (T)2107, (T)-5188, (T)1854, (T)3708, (T)-2788, (T)547);
-    } else {
-        // FP64: the sum-of-squares form (no cancellation)
-        g0 = a1_0 * (a1_0 + kk * a3_0) + (a2_0 * a2_0 + (a3_0 * a3_0 + eps));
-        g1 = a1_1 * (a1_1 + kk * a3_1) + (a2_1 * a2_1 + (a3_1 * a3_1 + eps));
-        g2 = a1_2 * (a1_2 + kk * a3_2) + (a2_1 * a2_1 + (a3_2 * a3_2 + eps));
-        g3 = a1_3 * (a1_3 + kk * a3_3) + (a2_3 * a2_3 + (a3_3 * a3_3 + eps));
-    }
-    g0 *= g0;
-    g1 *= g1;
-    g2 *= g2;
-    g3 *= g3;
+    const T q0 = (T)0.25 * D1 - (T)(5.0 / 6.0) * D2 + (T)(13.0 / 12.0) * D3;
+    const T q1 = ((T)4 * D3 - D2) + (T)3 * D4;
+    const T q2 = (T)1.5 * (D3 - D5) + (T)9 * D4;
+    const T q3 = ((T)3 * D4 - (T)(4.0 / 3.0) * D5) + (T)(1.0 / 3.0) * D6;
+    const Smooth7<T> S = smooth7<T>(D1, D2, D3, D4, D5, D6, eps);
+    const T g0 = S.g0 * S.g0, g1 = S.g1 * S.g1, g2 = S.g2 * S.g2, g3 = S.g3 * S.g3;
     if constexpr (sizeof(T) == 8) {
-        // FP64: one reciprocal via products of the other three squared terms
+        // FP64: one reciprocal, the weights multiplied through by g0 g1 g2 g3
         const T g01 = g0 * g1, g23 = g2 * g3;
-        const T w0 = (T)(1.0 / 35.0) * (g1 * g23);
-        const T w1 = (T)(12.0 / 35.0) * (g0 * g23);
-        const T w2 = (T)(18.0 / 35.0) * (g01 * g3);
-        const T w3 = (T)(4.0 / 35.0) * (g01 * g2);
-        const T num = (w0 * dq0 + w1 * dq1) + (w2 * dq2 + w3 * dq3);
-        const T den = (w0 + w1) + (w2 + w3);
+        const T num = g23 * (g1 * q0 + g0 * q1) + g01 * (g3 * q2 + g2 * q3);
+        const T den = g23 * (g1 + (T)12 * g0) + g01 * ((T)18 * g3 + (T)4 * g2);
         return s3 + num * fast_rcp(den);
     } else {
         // FP32: products of three squared terms can overflow, so one reciprocal
-        // per weight; the linear weights 35 d = (1, 12, 18, 4) are folded into
-        // the candidates (12 dq1 = 4 D3 - D2 + 3 D4, 18 dq2 = 3/2 (D3 - D5) + 9 D4,
-        // 4 dq3 = 3 D4 - 4/3 D5 + 1/3 D6) and the weight sum, the 1/35 cancels
+        // per weight
         const T r0 = fast_rcp(g0), r1 = fast_rcp(g1), r2 = fast_rcp(g2), r3 = fast_rcp(g3);
-        const T q1 = ((T)4 * D3 - D2) + (T)3 * D4;
-        const T q2 = (T)1.5 * (D3 - D5) + (T)9 * D4;
-        const T q3 = ((T)3 * D4 - (T)(4.0 / 3.0) * D5) + (T)(1.0 / 3.0) * D6;
-        const T num = (r0 * dq0 + r1 * q1) + (r2 * q2 + r3 * q3);
+        const T num = (r0 * q0 + r1 * q1) + (r2 * q2 + r3 * q3);
         const T den = (r0 + (T)12 * r1) + ((T)18 * r2 + (T)4 * r3);
         return s3 + num * fast_rcp(den);
     }
