@@ -6,7 +6,8 @@
 // partials per cell; it writes the output from the caller's linear combination
 // plus its part.  On periodic rows of 32..256 cells it takes whole rows
 // (adj_xrow) and also computes and stores the pack; otherwise it takes tiles
-// (adj_x) after a separate pack launch (adj_pack).  The y and z sweeps (adj_roll)
+// (adj_tile) after a separate pack launch (adj_pack).  The y and z sweeps of small
+// grids take tiles as well; those of large grids (adj_roll)
 // give each lane a segment [k0, k1) of one grid line; the lane rolls along it
 // over every face whose stencil reaches an owned position (the segment plus R
 // faces on each side), keeping a register window of 2R cells of split fluxes
@@ -467,64 +468,86 @@ __global__ void adj_pack(const T* __restrict__ u, T* __restrict__ pk, long long 
 }
 
 // ---------------------------------------------------------------------------
-// x axis: x is contiguous, so a block takes a tile of TX cells x TY rows plus
-// ghosts in LDS, as the forward x sweep does.  Per component, each lane
-// differentiates one face (the tile's faces are spread over the lanes) and
-// writes the face's stencil partials to LDS; after a barrier each lane sums
-// the partials of the faces that reach its cell in a fixed order.  With all
-// five split-flux adjoints of its cell in registers the lane applies the flux
-// Jacobian once and writes out = (linear combination of init terms) + scale g.
+// Tiles: a block takes a tile of TX positions along the axis x TY lines plus
+// ghosts in LDS.  Per component, each lane differentiates one face (the tile's
+// faces are spread over the lanes) and writes the face's stencil partials to LDS;
+// after a barrier each lane sums the partials of the faces that reach its cell
+// in a fixed order.  With all five split-flux adjoints of its cell in registers
+// the lane applies the flux Jacobian once.  The x axis writes out = (linear
+// combination of init terms) + scale g; y and z add scale g to out.
 // Outflow ghost positions fold onto the edge cells (same state, so their
 // split-flux adjoints add before the Jacobian); analytic ghosts are constants.
+//
+// Lines are numbered so that consecutive ones are neighbours in memory: along x
+// a line is a row and lanes run along it, along y and z the lanes of a wave run
+// across the lines (x fastest), so every access is contiguous either way and the
+// LDS layout follows the lanes.
 // ---------------------------------------------------------------------------
-template <class T>
-__device__ __forceinline__ void x_state(const AdjArgs<T>& A, int gx, int row, T u[5], T& v, T& P) {
-    const int nx = A.n[0];
-    int mx = gx;
-    if (gx < 0 || gx >= nx) {
+// First cell of line `p` of the axis DIR and the step between its cells.
+template <int DIR>
+__device__ __forceinline__ long long line_cell(const int n[3], int p, int m) {
+    if constexpr (DIR == 0) return m + (long long)n[0] * p;
+    else if constexpr (DIR == 1) return p % n[0] + (long long)n[0] * (m + (long long)n[1] * (p / n[0]));
+    else return p + (long long)n[0] * n[1] * m;
+}
+
+// State, velocity along the axis and pressure at position m of a line.
+template <class T, int DIR>
+__device__ __forceinline__ void line_state(const AdjArgs<T>& A, int m, int line, T u[5], T& v, T& P) {
+    const int nd = A.n[DIR];
+    int mm = m;
+    if (m < 0 || m >= nd) {
         if (A.bc == RH_BC_PERIODIC) {
-            mx = gx % nx;
-            if (mx < 0) mx += nx;
+            mm = m % nd;
+            if (mm < 0) mm += nd;
         } else if (A.bc == RH_BC_OUTFLOW) {
-            mx = gx < 0 ? 0 : nx - 1;
+            mm = m < 0 ? 0 : nd - 1;
         } else {
-            const int y = row % A.n[1], z = row / A.n[1];
+            int c[3];
+            if (DIR == 0) { c[0] = m; c[1] = line % A.n[1]; c[2] = line / A.n[1]; }
+            else if (DIR == 1) { c[0] = line % A.n[0]; c[1] = m; c[2] = line / A.n[0]; }
+            else { c[0] = line % A.n[0]; c[1] = line / A.n[0]; c[2] = m; }
             double uh[5];
-            hubble_conserved(A.hb, A.hb.c0[0] + gx * A.hb.h[0], A.hb.c0[1] + y * A.hb.h[1],
-                             A.hb.c0[2] + z * A.hb.h[2], uh);
+            hubble_conserved(A.hb, A.hb.c0[0] + c[0] * A.hb.h[0], A.hb.c0[1] + c[1] * A.hb.h[1],
+                             A.hb.c0[2] + c[2] * A.hb.h[2], uh);
 #pragma unroll
             for (int f = 0; f < 5; ++f) u[f] = (T)uh[f];
             double vd, pd;
             unsigned dummy = 0;
-            recover_vp<0>(uh[0], uh[1], uh[2], uh[3], vd, pd, dummy);
+            recover_vp<DIR>(uh[0], uh[1], uh[2], uh[3], vd, pd, dummy);
             v = (T)vd;
             P = (T)pd;
             return;
         }
     }
-    const long long id = mx + (long long)nx * row;
+    const long long id = line_cell<DIR>(A.n, line, mm);
 #pragma unroll
     for (int f = 0; f < 5; ++f) u[f] = A.u[f * A.fstride + id];
-    v = A.pk[id] * u[1];
+    v = A.pk[id] * u[1 + DIR];
     P = A.pk[A.fstride + id];
 }
 
-template <class T, int ORDER, int TX, int TY>
-__global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
+template <class T, int ORDER, int DIR, int TX, int TY>
+__global__ void __launch_bounds__(256) adj_tile(AdjArgs<T> A, Lin3<T> init) {
     constexpr int R = (ORDER + 1) / 2, K = 2 * R - 1;
     constexpr int CPL = TX * TY / 256;   // cells per lane
     constexpr int NF = TX + 2 * R - 1;   // faces x0-R .. x0+TX+R-2 (face i: between cells i and i+1)
     constexpr int NC = TX + 4 * R - 2;   // cells x0-2R+1 .. x0+TX+2R-2
     constexpr int NW = TX + 2 * R;       // weights x0-R .. x0+TX+R-1
     static_assert(TX * TY % 256 == 0, "whole cells per lane");
-    __shared__ T sfp[5][TY][NC];
-    __shared__ T sfm[5][TY][NC];
-    __shared__ T sw[5][TY][NW];
-    __shared__ T sp[TY][NF][K];          // plus partials of face fl for cells fl .. fl+K-1 (local)
-    __shared__ T sm[TY][NF][K];          // minus partials of face fl for cells fl+1 .. fl+K
-    const int nx = A.n[0];
-    const int nrows = A.n[1] * A.n[2];
-    const int ntx = (nx + TX - 1) / TX;
+    constexpr bool ALONG = DIR == 0;     // lanes run along the line, else across the lines
+    // LDS strides of (position, line): the lanes' direction is the fast one
+    constexpr int CX = ALONG ? 1 : TY, CY = ALONG ? NC : 1, WY = ALONG ? NW : 1, FY = ALONG ? NF : 1;
+    __shared__ T sfp[5][TY * NC];
+    __shared__ T sfm[5][TY * NC];
+    __shared__ T sw[5][TY * NW];
+    __shared__ T sp[TY * NF * K];        // plus partials of face fl for cells fl .. fl+K-1 (local)
+    __shared__ T sm[TY * NF * K];        // minus partials of face fl for cells fl+1 .. fl+K
+    // partials: x keeps a face's K values together, y and z a line's neighbours
+    auto part = [](int ly, int fl, int k) { return ALONG ? (ly * NF + fl) * K + k : (fl * K + k) * TY + ly; };
+    const int nd = A.n[DIR];
+    const int nlines = DIR == 0 ? A.n[1] * A.n[2] : DIR == 1 ? A.n[0] * A.n[2] : A.n[0] * A.n[1];
+    const int ntx = (nd + TX - 1) / TX;
     const int bx = blockIdx.x % ntx, by = blockIdx.x / ntx;
     const int x0 = bx * TX, r0 = by * TY;
     const int tid = threadIdx.x;
@@ -532,46 +555,36 @@ __global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
     const T half = (T)0.5;
 
     for (int idx = tid; idx < TY * NC; idx += 256) {
-        const int ly = idx / NC, lx = idx - ly * NC;
-        const int row = r0 + ly;
+        const int ly = ALONG ? idx / NC : idx % TY, lx = ALONG ? idx - ly * NC : idx / TY;
+        const int line = r0 + ly;
         T fp[5] = {(T)0, (T)0, (T)0, (T)0, (T)0}, fm[5] = {(T)0, (T)0, (T)0, (T)0, (T)0};
-        if (row < nrows) {
+        if (line < nlines) {
             T u[5], v, P;
-            x_state<T>(A, x0 - 2 * R + 1 + lx, row, u, v, P);
-            T f[5];
-            f[0] = u[1];
-            f[1] = u[1] * v + P;
-            f[2] = u[2] * v;
-            f[3] = u[3] * v;
-            f[4] = u[4] * v;
-#pragma unroll
-            for (int c = 0; c < 5; ++c) {
-                fp[c] = f[c] + u[c];   // doubled split fluxes (eps scaled by 4 below)
-                fm[c] = f[c] - u[c];
-            }
+            line_state<T, DIR>(A, x0 - 2 * R + 1 + lx, line, u, v, P);
+            split_flux_vp<T, DIR>(u, v, P, fp, fm);   // doubled split fluxes (eps scaled by 4 below)
         }
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
-            sfp[c][ly][lx] = fp[c];
-            sfm[c][ly][lx] = fm[c];
+            sfp[c][idx] = fp[c];
+            sfm[c][idx] = fm[c];
         }
     }
     for (int idx = tid; idx < TY * NW; idx += 256) {
-        const int ly = idx / NW, lx = idx - ly * NW;
-        const int row = r0 + ly;
+        const int ly = ALONG ? idx / NW : idx % TY, lx = ALONG ? idx - ly * NW : idx / TY;
+        const int line = r0 + ly;
         int gx = x0 - R + lx;
-        bool inside = row < nrows;
-        if (inside && (gx < 0 || gx >= nx)) {
+        bool inside = line < nlines;
+        if (inside && (gx < 0 || gx >= nd)) {
             if (periodic) {
-                gx %= nx;
-                if (gx < 0) gx += nx;
+                gx %= nd;
+                if (gx < 0) gx += nd;
             } else {
                 inside = false;   // weights vanish outside a non-periodic grid
             }
         }
-        const long long id = gx + (long long)nx * row;
+        const long long id = inside ? line_cell<DIR>(A.n, line, gx) : 0;
 #pragma unroll
-        for (int c = 0; c < 5; ++c) sw[c][ly][lx] = inside ? A.w[c * A.fstride + id] : (T)0;
+        for (int c = 0; c < 5; ++c) sw[c][idx] = inside ? A.w[c * A.fstride + id] : (T)0;
     }
     __syncthreads();
 
@@ -579,24 +592,26 @@ __global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
 #pragma unroll 1
     for (int c = 0; c < 5; ++c) {
         for (int f = tid; f < TY * NF; f += 256) {
-            const int fy = f / NF, fl = f - fy * NF;
+            const int fy = ALONG ? f / NF : f % TY, fl = ALONG ? f - fy * NF : f / TY;
             const int i = x0 - R + fl;
             T op[K], om[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) op[k] = om[k] = (T)0;
-            if ((periodic || (i >= -1 && i <= nx - 1)) && r0 + fy < nrows) {
-                const T g = (sw[c][fy][fl + 1] - sw[c][fy][fl]) * A.inv_h;
+            if ((periodic || (i >= -1 && i <= nd - 1)) && r0 + fy < nlines) {
+                const T* wf = &sw[c][fl * CX + fy * WY];
+                const T* cp = &sfp[c][fl * CX + fy * CY];
+                const T* cm = &sfm[c][fl * CX + fy * CY];
+                const T g = (wf[CX] - wf[0]) * A.inv_h;
                 if constexpr (ORDER == 5) {
-                    weno5_grad_acc_e<T>(sfp[c][fy][fl], sfp[c][fy][fl + 1], sfp[c][fy][fl + 2], sfp[c][fy][fl + 3],
-                                      sfp[c][fy][fl + 4], (T)16 * A.eps, g, op[0], op[1], op[2], op[3], op[4]);
-                    weno5_grad_acc_e<T>(sfm[c][fy][fl + 5], sfm[c][fy][fl + 4], sfm[c][fy][fl + 3],
-                                      sfm[c][fy][fl + 2], sfm[c][fy][fl + 1], (T)16 * A.eps, g, om[4], om[3],
-                                      om[2], om[1], om[0]);
+                    weno5_grad_acc_e<T>(cp[0], cp[CX], cp[2 * CX], cp[3 * CX], cp[4 * CX], (T)16 * A.eps, g, op[0],
+                                        op[1], op[2], op[3], op[4]);
+                    weno5_grad_acc_e<T>(cm[5 * CX], cm[4 * CX], cm[3 * CX], cm[2 * CX], cm[CX], (T)16 * A.eps, g,
+                                        om[4], om[3], om[2], om[1], om[0]);
                 } else {
                     T sv[7], o[7];
 #pragma unroll
                     for (int j = 0; j < 7; ++j) {
-                        sv[j] = sfp[c][fy][fl + j];
+                        sv[j] = cp[j * CX];
                         o[j] = (T)0;
                     }
                     weno7_grad_acc<T>(sv, (T)4 * A.eps, g, o);
@@ -604,7 +619,7 @@ __global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
                     for (int j = 0; j < 7; ++j) op[j] = o[j];
 #pragma unroll
                     for (int j = 0; j < 7; ++j) {
-                        sv[j] = sfm[c][fy][fl + 7 - j];
+                        sv[j] = cm[(7 - j) * CX];
                         o[j] = (T)0;
                     }
                     weno7_grad_acc<T>(sv, (T)4 * A.eps, g, o);
@@ -614,31 +629,32 @@ __global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
             }
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                sp[fy][fl][k] = op[k];
-                sm[fy][fl][k] = om[k];
+                sp[part(fy, fl, k)] = op[k];
+                sm[part(fy, fl, k)] = om[k];
             }
         }
         __syncthreads();
         // partials reaching staged cell q: plus from faces q-k, minus from faces q-1-k
 #pragma unroll
         for (int j = 0; j < CPL; ++j) {
-            const int cell = tid + 256 * j, lx = cell % TX, ly = cell / TX;
+            const int cell = tid + 256 * j;
+            const int lx = ALONG ? cell % TX : cell / TY, ly = ALONG ? cell / TX : cell % TY;
             const int q = lx + 2 * R - 1;   // every face reaching an owned cell is in the tile
             T a_p = (T)0, a_m = (T)0;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                a_p += sp[ly][q - k][k];
-                a_m += sm[ly][q - 1 - k][k];
+                a_p += sp[part(ly, q - k, k)];
+                a_m += sm[part(ly, q - 1 - k, k)];
             }
             const int gx = x0 + lx;
-            if (A.bc == RH_BC_OUTFLOW && (gx == 0 || gx == nx - 1) && r0 + ly < nrows) {
+            if (A.bc == RH_BC_OUTFLOW && (gx == 0 || gx == nd - 1) && r0 + ly < nlines) {
                 // ghost positions beyond the edge fold onto the edge cell
                 for (int e = 1; e < 2 * R; ++e) {
                     const int qe = gx == 0 ? q - e : q + e;
                     for (int k = 0; k < K; ++k) {
                         const int fp_ = qe - k, fm_ = qe - 1 - k;
-                        if (fp_ >= 0 && fp_ < NF) a_p += sp[ly][fp_][k];
-                        if (fm_ >= 0 && fm_ < NF) a_m += sm[ly][fm_][k];
+                        if (fp_ >= 0 && fp_ < NF) a_p += sp[part(ly, fp_, k)];
+                        if (fm_ >= 0 && fm_ < NF) a_m += sm[part(ly, fm_, k)];
                     }
                 }
             }
@@ -649,10 +665,11 @@ __global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
     }
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
-        const int cell = tid + 256 * j, lx = cell % TX, ly = cell / TX;
-        const int gx = x0 + lx, row = r0 + ly;
-        if (gx >= nx || row >= nrows) continue;
-        const long long id = gx + (long long)nx * row;
+        const int cell = tid + 256 * j;
+        const int lx = ALONG ? cell % TX : cell / TY, ly = ALONG ? cell / TX : cell % TY;
+        const int gx = x0 + lx, line = r0 + ly;
+        if (gx >= nd || line >= nlines) continue;
+        const long long id = line_cell<DIR>(A.n, line, gx);
         T uf[5];
 #pragma unroll
         for (int f = 0; f < 5; ++f) uf[f] = A.u[f * A.fstride + id];
@@ -664,28 +681,32 @@ __global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
             lam[c] = half * (ap[j][c] + am[j][c]);
             g[c] = half * (ap[j][c] - am[j][c]);
         }
-        // F = (Mx, Mx v + p, My v, Mz v, N v) with v = kappa Mx
-        const T Mx = uf[1], vd = kap * Mx;
-        g[1] += lam[0];
+        // F = (M_d, M v + p e_d, N v) with v = kappa M_d
+        const T Md = uf[1 + DIR], vd = kap * Md;
+        g[1 + DIR] += lam[0];
         T S = (T)0;
 #pragma unroll
         for (int c = 1; c < 5; ++c) {
             S += lam[c] * uf[c];
             g[c] += lam[c] * vd;
         }
-        const T lp = lam[1];
-        g[0] += S * (Mx * kE) + lp * pE;
-        const T sk = (T)2 * S * Mx * kM2, spp = (T)2 * lp * pM2;
+        const T lp = lam[1 + DIR];
+        g[0] += S * (Md * kE) + lp * pE;
+        const T sk = (T)2 * S * Md * kM2, spp = (T)2 * lp * pM2;
 #pragma unroll
         for (int m = 0; m < 3; ++m) g[1 + m] += (sk + spp) * uf[1 + m];
-        g[1] += S * kap;
+        g[1 + DIR] += S * kap;
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
             const long long o = f * A.fstride + id;
             T acc = (T)0;
-            if (init.X1) acc += init.a1 * init.X1[o];
-            if (init.X2) acc += init.a2 * init.X2[o];
-            if (init.X3) acc += init.a3 * init.X3[o];
+            if constexpr (DIR == 0) {
+                if (init.X1) acc += init.a1 * init.X1[o];
+                if (init.X2) acc += init.a2 * init.X2[o];
+                if (init.X3) acc += init.a3 * init.X3[o];
+            } else {
+                acc = A.ub[o];
+            }
             A.ub[o] = acc + A.scale * g[f];
         }
     }
@@ -699,7 +720,7 @@ __global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
 // and gathers the partials of the faces that reach its cell.  No lane stages a
 // ghost from HBM or differentiates a halo face, which the tiled kernel does for
 // 2R - 1 faces per row (a fifth of its face rounds at 64 x 4).  The arithmetic
-// and the order of every sum are those of adj_x, so both give the same bits.
+// and the order of every sum are those of adj_tile, so both give the same bits.
 // ---------------------------------------------------------------------------
 // FP32 WENO5 rows: six waves per SIMD, the most that the LDS of 256-cell row
 // blocks allows (62 registers instead of 82; 0.5% faster at 256^3).
@@ -924,16 +945,54 @@ static unsigned blocks_for(long long n) {
     return (unsigned)b;
 }
 
+// Grids whose y and z adjoint take tiles.  A rolling lane differentiates every
+// face that reaches its segment, 2R - 1 more than it owns, one after another; a
+// tile differentiates each face once (and those of its ghosts) with all lanes,
+// but pays ten barriers and its staging.  Measured for J^T w, tiles against rolls
+// at their best segment: 40 x 36 x 28 FP64 WENO7 60 against 134 us (219 at segments of
+// 16), 64^3 FP32 WENO5 62 against 64, FP64 WENO7 124 against 145; 96^3 161 against
+// 138 and 381 against 376.
+bool adjoint_tiles(const int n[3]) { return (long long)n[0] * n[1] * n[2] < 400000; }
+
+// Segment of the rolling adjoint: the longest of 24, 16 and 8 positions (each
+// segment differentiates 2R - 1 extra faces) that still gives two blocks per CU;
+// FP64 blocks fill their CU, so one block on most CUs is enough there.  96^3 FP32 WENO5
+// 159 us at 16, 138 at 8; FP64 WENO7 376 at 16, 407 at 8; 256^3 FP32 WENO5 1700 at 32,
+// 1608 at 24, FP64 4235 and 4041.
+int adjoint_segment(int nd, unsigned chunks, int elem) {
+    for (int seg : {24, 16, 8}) {
+        const long long blocks = (long long)chunks * ((nd + seg - 1) / seg);
+        if (blocks >= (elem == 8 && seg == 16 ? 200 : 512)) return seg < nd ? seg : nd;
+    }
+    return nd < 8 ? nd : 8;
+}
+
+template <class T, int ORDER, int DIR, int TX>
+static void launch_adjoint_tiles(const AdjArgs<T>& a, long long nlines, hipStream_t s) {
+    constexpr int TY = 256 / TX;
+    const Lin3<T> none = {(T)0, (T)0, (T)0, nullptr, nullptr, nullptr};
+    const long long ntx = (a.n[DIR] + TX - 1) / TX, nrt = (nlines + TY - 1) / TY;
+    adj_tile<T, ORDER, DIR, TX, TY><<<dim3((unsigned)(ntx * nrt)), 256, 0, s>>>(a, none);
+}
+
 template <class T>
 hipError_t launch_adjoint_sweep(int dir, int order, AdjArgs<T> a, hipStream_t s) {
+    if ((dir != 1 && dir != 2) || !a.pk) return hipErrorInvalidValue;
     const int nd = a.n[dir];
-    const long long plane = dir == 0 ? (long long)a.n[1] * a.n[2]
-                          : dir == 1 ? (long long)a.n[0] * a.n[2] : (long long)a.n[0] * a.n[1];
+    const long long plane = dir == 1 ? (long long)a.n[0] * a.n[2] : (long long)a.n[0] * a.n[1];
+    if (adjoint_tiles(a.n)) {
+        // WENO7 tiles are 32 x 8: the LDS of a 16 x 16 tile (95 KB in FP64) keeps a
+        // second block off the CU (64^3 FP64: 124 against 167 us per J^T w; WENO5 FP32 75 against 62)
+        if (order == 5 && dir == 1) launch_adjoint_tiles<T, 5, 1, 16>(a, plane, s);
+        else if (order == 5) launch_adjoint_tiles<T, 5, 2, 16>(a, plane, s);
+        else if (dir == 1) launch_adjoint_tiles<T, 7, 1, 32>(a, plane, s);
+        else launch_adjoint_tiles<T, 7, 2, 32>(a, plane, s);
+        return hipGetLastError();
+    }
     const unsigned gx = (unsigned)((plane + 255) / 256);
-    a.seg = choose_segment(nd, (int)(gx * 256));
+    a.seg = adjoint_segment(nd, gx, (int)sizeof(T));
     const unsigned gy = (nd + a.seg - 1) / a.seg;
     const dim3 grid(gx, gy), block(256);
-    if ((dir != 1 && dir != 2) || !a.pk) return hipErrorInvalidValue;
     const bool hub = a.bc == RH_BC_HUBBLE;
     auto go = [&](auto kernel) { kernel<<<grid, block, 0, s>>>(a); };
     if (order == 5) {
@@ -990,13 +1049,13 @@ hipError_t launch_adjoint_x(int order, AdjArgs<T> a, Lin3<T> init, hipStream_t s
     const long long nrt = ((long long)a.n[1] * a.n[2] + ty - 1) / ty;
     const dim3 grid((unsigned)(ntx * nrt));
     if (order == 5) {
-        if (tx == 64) adj_x<T, 5, 64, 4><<<grid, 256, 0, s>>>(a, init);
-        else if (tx == 32) adj_x<T, 5, 32, 8><<<grid, 256, 0, s>>>(a, init);
-        else adj_x<T, 5, 16, 16><<<grid, 256, 0, s>>>(a, init);
+        if (tx == 64) adj_tile<T, 5, 0, 64, 4><<<grid, 256, 0, s>>>(a, init);
+        else if (tx == 32) adj_tile<T, 5, 0, 32, 8><<<grid, 256, 0, s>>>(a, init);
+        else adj_tile<T, 5, 0, 16, 16><<<grid, 256, 0, s>>>(a, init);
     } else {
-        if (tx == 64) adj_x<T, 7, 64, 4><<<grid, 256, 0, s>>>(a, init);
-        else if (tx == 32) adj_x<T, 7, 32, 8><<<grid, 256, 0, s>>>(a, init);
-        else adj_x<T, 7, 16, 16><<<grid, 256, 0, s>>>(a, init);
+        if (tx == 64) adj_tile<T, 7, 0, 64, 4><<<grid, 256, 0, s>>>(a, init);
+        else if (tx == 32) adj_tile<T, 7, 0, 32, 8><<<grid, 256, 0, s>>>(a, init);
+        else adj_tile<T, 7, 0, 16, 16><<<grid, 256, 0, s>>>(a, init);
     }
     return hipGetLastError();
 }

@@ -136,3 +136,49 @@ def test_row_vjp_is_bitwise_the_tiled_kernel(tmp_path):
                 h.close()
                 tiled = np.load("%s_%s_%d_%d.npy" % (out, name, o, shape[0]))
                 assert np.array_equal(got, tiled), (name, o, shape, np.abs(got - tiled).max())
+
+
+LARGE = {
+    # above the size from which y and z roll instead of taking tiles; ragged axes
+    "periodic": lambda o: inputs.random_smooth((76, 75, 71), h=0.1, seed=301, order=o),
+    "outflow": lambda o: inputs.random_smooth((61, 83, 81), h=0.1, seed=302, order=o, bc=(inputs.BC_OUTFLOW,) * 3),
+    "hubble": lambda o: inputs.hubble(n=75, order=o, half_width=3.0),
+}
+# below it: one short of, at and past a tile edge along every axis
+SMALL = {
+    "edge_15_16_17": lambda o: inputs.random_smooth((15, 16, 17), h=0.1, seed=303, order=o),
+    "edge_33_31_32": lambda o: inputs.random_smooth((33, 31, 32), h=0.1, seed=304, order=o, bc=(inputs.BC_OUTFLOW,) * 3),
+    "two_cells": lambda o: inputs.random_smooth((9, 2, 3), h=0.1, seed=305, order=o, bc=(inputs.BC_OUTFLOW,) * 3),
+    "hubble": lambda o: inputs.hubble(n=18, order=o, half_width=3.0),
+}
+
+
+@pytest.mark.parametrize("order", [5, 7])
+@pytest.mark.parametrize("case", sorted(LARGE) + sorted("small_" + k for k in SMALL))
+def test_yz_adjoint_tiles_and_rolls_match_reference(case, order):
+    """FP64 J^T w on both sides of the size at which the y and z adjoint change
+    kernel, to the 1e-12 of the other adjoint tests.
+    The reference is the gradient of the plain 64-bit right-hand side of the
+    measured workloads (the oracle's own WENO7 adjoint is 3e-12 from it at the
+    edge of the ragged outflow grid, the library 3e-13)."""
+    import importlib.util
+    import os
+
+    import torch
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    mod = importlib.util.spec_from_file_location("measured_cases", os.path.join(root, "perf", "cases.py"))
+    cases = importlib.util.module_from_spec(mod)
+    rh = rh_module()
+    mod.loader.exec_module(cases)
+    spec = (SMALL[case[6:]] if case.startswith("small_") else LARGE[case])(order)
+    u = oracle.prim2con(spec["prim"])
+    w = np.random.default_rng(9).normal(size=u.shape)
+    t = spec["t0"] + 0.1
+    h = rh.Hydro.from_spec(spec, precision=rh.RH_PREC_FP64)
+    got = h.vjp(u, w, t=t).cpu().numpy()
+    h.close()
+    ut = torch.tensor(u, device="cuda", requires_grad=True)
+    L = cases._rhs(ut, dict(spec, lf_local=False, eos=0), t)
+    ref = torch.autograd.grad(L, ut, torch.tensor(w, device="cuda"))[0].cpu().numpy()
+    err = np.abs(got - ref).reshape(5, -1).max(axis=1) / max(np.abs(ref).max(), np.abs(w).max() / min(spec["h"]))
+    assert np.all(err <= 1e-12), err
