@@ -84,7 +84,9 @@ typedef int rh_status;
  * applies, and for other single grids the faster of the two: RH_PATH_STAGE for
  * three-dimensional grids below a size that depends on scheme, precision and
  * boundaries, RH_PATH_SWEEPS otherwise and while per-launch timing is on
- * (rh_set_timing), so that the times are those of the directional sweeps. */
+ * (rh_set_timing), so that the times are those of the directional sweeps.  On
+ * RH_PATH_AUTO rh_step advances one-dimensional grids of up to 8192 cells
+ * (periodic or outflow, any scheme) several steps per launch, without graphs. */
 #define RH_PATH_AUTO   0
 #define RH_PATH_SWEEPS 1
 #define RH_PATH_STAGE  2

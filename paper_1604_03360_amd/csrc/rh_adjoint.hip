@@ -537,7 +537,7 @@ __global__ void __launch_bounds__(256) adj_tile(AdjArgs<T> A, Lin3<T> init) {
     static_assert(TX * TY % 256 == 0, "whole cells per lane");
     constexpr bool ALONG = DIR == 0;     // lanes run along the line, else across the lines
     // LDS strides of (position, line): the lanes' direction is the fast one
-    constexpr int CX = ALONG ? 1 : TY, CY = ALONG ? NC : 1, WY = ALONG ? NW : 1, FY = ALONG ? NF : 1;
+    constexpr int CX = ALONG ? 1 : TY, CY = ALONG ? NC : 1, WY = ALONG ? NW : 1;
     __shared__ T sfp[5][TY * NC];
     __shared__ T sfm[5][TY * NC];
     __shared__ T sw[5][TY * NW];

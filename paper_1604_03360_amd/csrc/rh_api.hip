@@ -418,12 +418,75 @@ rh_status capture_steps(rh_plan* p, double dt, double t, int count, hipGraph_t* 
     return RH_OK;
 }
 
+// Axis of a one-dimensional grid whose steps the line kernel takes, or -1.  It
+// beats a launch per stage while its blocks (one per 16 or 32 cells) fit the chip
+// at once; explicit paths, per-launch timing and analytic boundaries keep the
+// launches per stage.
+int line_axis(const rh_plan* p) {
+    const int n[3] = {p->d.nx, p->d.ny, p->d.nz};
+    int axis = -1;
+    for (int d = 0; d < 3; ++d) {
+        if (n[d] < 2) continue;
+        if (axis >= 0) return -1;
+        axis = d;
+    }
+    if (axis < 0 || p->path != RH_PATH_AUTO || p->timing || n[axis] > rh::kLineMaxCells ||
+        p->d.bc[axis] == RH_BC_HUBBLE)
+        return -1;
+    return axis;
+}
+
+// n steps of a one-dimensional grid along `axis`: as few launches as the steps
+// per launch allow, alternating between the state and the workspace (an even
+// number of them, or a copy back when there is a single step), or in place for
+// a line that fits one block.
+template <class T>
+rh_status line_steps_impl(rh_plan* p, int axis, double dt, int nsteps) {
+    const double h[3] = {p->d.dx, p->d.dy, p->d.dz};
+    rh::LineArgs<T> a;
+    std::memset(&a, 0, sizeof(a));
+    a.n = (int)p->ncell;
+    a.dir = axis;
+    a.bc = p->d.bc[axis];
+    a.inv_h = (T)(1.0 / h[axis]);
+    a.dt = (T)dt;
+    a.eps = (T)(p->d.weno_eps > 0.0 ? p->d.weno_eps : 1e-6);
+    a.gm1 = eos_gm1(p->d);
+    a.limiter = p->d.limiter;
+    a.mk = p->d.musta_stages;
+    a.lam = (T)p->d.musta_cfl;
+    a.clamps = p->d_clamps;
+    T* state = (T*)p->state;
+    T* other = a.n <= rh::kLineSingle ? state : (T*)p->ws;
+    const int most = rh::line_max_steps(p->d.scheme, (int)sizeof(T), a.n);
+    int launches = (nsteps + most - 1) / most;
+    if (other != state && launches % 2 == 1 && nsteps > launches) ++launches;
+    T* from = state;
+    for (int k = 0, done = 0; k < launches; ++k) {
+        T* to = from == state ? other : state;
+        a.in = from;
+        a.out = to;
+        a.steps = (nsteps - done) / (launches - k);
+        done += a.steps;
+        const hipError_t e = rh::launch_line<T>(p->d.scheme, p->d.flux_split == RH_SPLIT_LOCAL, p->d.eos, a, p->stream);
+        if (e != hipSuccess) return hip_fail(e, "line launch");
+        from = to;
+    }
+    if (from != state) {
+        const hipError_t e = hipMemcpyAsync(state, from, 5 * (size_t)p->ncell * sizeof(T), hipMemcpyDeviceToDevice, p->stream);
+        if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
+    }
+    return RH_OK;
+}
+
 // n steps: eager launches, or replays of captured steps when graphs are on
 // (kGraphSteps steps per replay while at least that many remain, then single
 // steps; not with analytic boundaries, whose stage times change every step,
 // and not while per-launch timing is on)
 template <class T>
 rh_status step_impl(rh_plan* p, double dt, int nsteps, double t, T* stages = nullptr) {
+    const int axis = stages ? -1 : line_axis(p);
+    if (axis >= 0) return line_steps_impl<T>(p, axis, dt, nsteps);
     const bool use_graph = p->graph_on && !stages && !any_hubble(p) && !p->timing;
     if (!use_graph) {
         for (int s = 0; s < nsteps; ++s) {

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "rh_device.hpp"
+#include "rh_face.hpp"
 #include "../../include/rh.h"
 
 namespace rh {
@@ -12,9 +13,6 @@ namespace rh {
 //   0: write L (accumulated over the directions done so far) to `lacc`;
 //   1..3: fuse the SSP-RK3 stage combine and write the new state to `uout`.
 enum { STAGE_WRITE_L = 0, STAGE_1 = 1, STAGE_2 = 2, STAGE_3 = 3 };
-
-// Equations of state of the kernels (the values of RH_EOS_*).
-enum { EOS_CONFORMAL = 0, EOS_IDEAL = 1 };
 
 template <class T>
 struct SweepArgs {
@@ -221,6 +219,31 @@ template <class T>
 // every grid of the launch (they select the kernel instance).
 hipError_t launch_musta(bool hub, int eos, int limiter, int mk, const StageArgs<T>& a, long long nblocks,
                         hipStream_t s);
+
+// ---------------------------------------------------------------------------
+// One-dimensional grids: several whole steps per launch
+// ---------------------------------------------------------------------------
+template <class T>
+struct LineArgs {
+    const T* in;        // state [5][n]
+    T* out;             // the state `steps` steps later; another buffer unless n <= kLineSingle
+    int n;              // cells of the line
+    int dir;            // axis the line runs along (0, 1, 2)
+    int bc;             // RH_BC_PERIODIC or RH_BC_OUTFLOW
+    int steps;          // SSP-RK3 steps, 1 .. line_max_steps()
+    T inv_h, dt, eps;
+    double gm1;         // ideal gas: gamma - 1
+    int limiter, mk;    // MUSTA-FORCE
+    T lam;
+    unsigned* clamps;   // floor counter
+    int tile, halo;     // set by the launcher
+};
+constexpr int kLineSingle = 96;      // longest line kept in one block
+constexpr int kLineMaxSteps = 256;   // steps per launch there
+constexpr int kLineMaxCells = 8192;  // 256 tiles of 32: one block per CU
+int line_max_steps(int scheme, int elem, int n);
+template <class T>
+hipError_t launch_line(int scheme, bool local, int eos, LineArgs<T> a, hipStream_t s);
 
 // The chip hands consecutive blocks of a launch to its eight XCDs in turn
 // (block b to XCD b mod 8).  Renumbering gives every XCD a contiguous range of

@@ -20,6 +20,7 @@
 // apart from the tile-edge faces, which both tiles compute.  The flux
 // difference is summed x, y, z and the stage combine is applied in place of
 // storing L.  Axes of one cell contribute nothing.
+#include "rh_face.hpp"
 #include "rh_internal.hpp"
 #include "../../include/rh.h"
 
@@ -30,82 +31,6 @@ namespace {
 constexpr int TX = kMustaTX, TY = kMustaTY;
 constexpr int G = 2;                 // ghost cells per side (MUSCL slopes of the end faces)
 constexpr int SX = TX + 2 * G, SY = TY + 2 * G;
-
-// Limiter and stage count of a kernel instance: fixed at compile time for the
-// default scheme (minmod, two stages: straight-line face code), read from the
-// grid entry otherwise.
-constexpr int kAnyLimiter = -1, kAnyStages = 0;
-
-// Limited MUSCL slope from the one-sided differences a, b (zero where they
-// differ in sign): minmod, MC, van Leer, superbee, or none.
-template <class T, int LIM>
-__device__ __forceinline__ T limited_slope(int rt_lim, T a, T b) {
-    const int lim = LIM == kAnyLimiter ? rt_lim : LIM;
-    if (lim == RH_LIMITER_NONE) return (T)0;
-    if (!((a > (T)0 && b > (T)0) || (a < (T)0 && b < (T)0))) return (T)0;
-    const T aa = fabs(a), ab = fabs(b);
-    T m;
-    if (lim == RH_LIMITER_MINMOD) m = min(aa, ab);
-    else if (lim == RH_LIMITER_MC) m = min(min((T)2 * aa, (T)2 * ab), (T)0.5 * (aa + ab));
-    else if (lim == RH_LIMITER_VANLEER) return (T)2 * a * b / (a + b);
-    else m = max(min((T)2 * aa, ab), min(aa, (T)2 * ab));
-    return a > (T)0 ? m : -m;
-}
-
-// Physical flux along DIR of a state (FP64 recovery for the fluid of EOS).
-template <class T, int DIR, int EOS>
-__device__ __forceinline__ void phys_flux(const T u[5], double gm1, T f[5], unsigned& cl) {
-    double vd, p;
-    if constexpr (EOS == EOS_CONFORMAL) {
-        recover_vp<DIR>((double)u[0], (double)u[1], (double)u[2], (double)u[3], vd, p, cl);
-    } else {
-        double kap, Mxs, Mys, Mzs, e;
-        recover_ideal((double)u[0], (double)u[1], (double)u[2], (double)u[3], (double)u[4], gm1, kap,
-                      Mxs, Mys, Mzs, p, e, cl);
-        vd = kap * (DIR == 0 ? Mxs : (DIR == 1 ? Mys : Mzs));
-    }
-    const T v = (T)vd, P = (T)p;
-    f[0] = u[1 + DIR];
-    f[1] = u[1] * v + (DIR == 0 ? P : (T)0);
-    f[2] = u[2] * v + (DIR == 1 ? P : (T)0);
-    f[3] = u[3] * v + (DIR == 2 ? P : (T)0);
-    f[4] = u[4] * v;
-}
-
-// MUSCL + MUSTA flux of face i+1/2 from the cells i-1 .. i+2 (a, b, c, d).
-template <class T, int DIR, int EOS, int LIM, int MK>
-__device__ __forceinline__ void musta_face(const T a[5], const T b[5], const T c[5], const T d[5],
-                                           const StageGrid<T>& Gr, T F[5], unsigned& cl) {
-    T uL[5], uR[5];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-        const T si = limited_slope<T, LIM>(Gr.limiter, b[q] - a[q], c[q] - b[q]);
-        const T sj = limited_slope<T, LIM>(Gr.limiter, c[q] - b[q], d[q] - c[q]);
-        uL[q] = b[q] + (T)0.5 * si;
-        uR[q] = c[q] - (T)0.5 * sj;
-    }
-    const T lam = Gr.lam, hlam = (T)0.5 * Gr.lam, q4 = (T)1 / ((T)4 * Gr.lam);
-    const int mk = MK == kAnyStages ? Gr.mk : MK;
-    constexpr int kUnroll = MK == kAnyStages ? 1 : MK;
-#pragma unroll kUnroll
-    for (int st = 1; st <= mk; ++st) {
-        T fL[5], fR[5], uM[5], fM[5];
-        phys_flux<T, DIR, EOS>(uL, Gr.gm1, fL, cl);
-        phys_flux<T, DIR, EOS>(uR, Gr.gm1, fR, cl);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) uM[q] = (T)0.5 * (uL[q] + uR[q]) - hlam * (fR[q] - fL[q]);
-        phys_flux<T, DIR, EOS>(uM, Gr.gm1, fM, cl);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) F[q] = (T)0.25 * (fL[q] + (T)2 * fM[q] + fR[q]) - (uR[q] - uL[q]) * q4;
-        if (st < mk) {
-#pragma unroll
-            for (int q = 0; q < 5; ++q) {
-                uL[q] = uL[q] - lam * (F[q] - fL[q]);
-                uR[q] = uR[q] - lam * (fR[q] - F[q]);
-            }
-        }
-    }
-}
 
 }  // namespace
 
@@ -173,6 +98,7 @@ __global__ void __launch_bounds__(256, (MustaMinBlocks<T>::value)) stage_musta(S
         if (hkind) stage_load<T, HUB>(Gr, us, F, t, x0 + hc, y0 + hr, m, u);
     };
 
+    const MustaFace<T> mf = {Gr.lam, Gr.gm1, Gr.limiter, Gr.mk};
     const T ihx = Gr.inv_h[0], ihy = Gr.inv_h[1], ihz = Gr.inv_h[2];
     unsigned clamped = 0;
 
@@ -229,7 +155,7 @@ __global__ void __launch_bounds__(256, (MustaMinBlocks<T>::value)) stage_musta(S
                         d[c] = su[c][r + G][f + 3];
                     }
                     unsigned cl = 0;
-                    musta_face<T, 0, EOS, LIM, MK>(a, bb, c2, d, Gr, Fx, cl);
+                    musta_face<T, 0, EOS, LIM, MK>(a, bb, c2, d, mf, Fx, cl);
                     if (f > 0 || x0 == 0) clamped += cl;   // each face of the grid counted once
 #pragma unroll
                     for (int c = 0; c < 5; ++c) fxs[c][r][f] = Fx[c];
@@ -248,7 +174,7 @@ __global__ void __launch_bounds__(256, (MustaMinBlocks<T>::value)) stage_musta(S
                         d[c] = su[c][f + 3][col + G];
                     }
                     unsigned cl = 0;
-                    musta_face<T, 1, EOS, LIM, MK>(a, bb, c2, d, Gr, Fy, cl);
+                    musta_face<T, 1, EOS, LIM, MK>(a, bb, c2, d, mf, Fy, cl);
                     if (f > 0 || y0 == 0) clamped += cl;
 #pragma unroll
                     for (int c = 0; c < 5; ++c) fys[c][f][col] = Fy[c];
@@ -269,7 +195,7 @@ __global__ void __launch_bounds__(256, (MustaMinBlocks<T>::value)) stage_musta(S
             T Fz[5];
             if (doz) {
                 unsigned cl = 0;
-                musta_face<T, 2, EOS, LIM, MK>(zw[0], zw[1], zw[2], zw[3], Gr, Fz, cl);
+                musta_face<T, 2, EOS, LIM, MK>(zw[0], zw[1], zw[2], zw[3], mf, Fz, cl);
                 if (act && (m - 2 >= k0 || k0 == 0)) clamped += cl;
             } else {
 #pragma unroll

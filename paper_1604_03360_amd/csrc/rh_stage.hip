@@ -38,29 +38,11 @@
 // solves for every cell's velocity and pressure once per evaluation of L, and
 // the stage reads them with the state).  An axis of one cell contributes
 // nothing to L.
+#include "rh_face.hpp"
 #include "rh_internal.hpp"
 #include "../../include/rh.h"
 
 namespace rh {
-
-namespace {
-
-// One reconstruction from a window of 2R doubled split fluxes of cells
-// i - R + 1 .. i + R (interface i + 1/2): plus = left-biased on f+, minus =
-// mirrored on f-.  eps2 is the epsilon of the doubled data (4 eps); WENO5
-// carries its smoothness indicators as 4 beta and takes 4 eps2.
-template <class T, int ORDER>
-__device__ __forceinline__ T stage_recon_plus(const T* w, T eps2) {
-    if constexpr (ORDER == 5) return weno5<T>(w[0], w[1], w[2], w[3], w[4], (T)4 * eps2);
-    else return weno7<T>(w[0], w[1], w[2], w[3], w[4], w[5], w[6], eps2);
-}
-template <class T, int ORDER>
-__device__ __forceinline__ T stage_recon_minus(const T* w, T eps2) {
-    if constexpr (ORDER == 5) return weno5<T>(w[5], w[4], w[3], w[2], w[1], (T)4 * eps2);
-    else return weno7<T>(w[7], w[6], w[5], w[4], w[3], w[2], w[1], eps2);
-}
-
-}  // namespace
 
 // Minimum resident blocks per CU (= waves per SIMD) for the register budget;
 // FP64 blocks other than WENO5 16 x 16 with global splitting need more than
@@ -69,22 +51,6 @@ template <class T, int ORDER, int TX, bool LOCAL>
 struct StageMinBlocks {
     static constexpr int value = sizeof(T) == 4 ? (ORDER == 5 && !LOCAL ? 3 : 2) : (ORDER == 5 && TX == 16 && !LOCAL ? 2 : 1);
 };
-
-// One face from the staged pairs of its 2R stencil cells: global splitting
-// stages (F + u, F - u) and reconstructs them directly; local splitting stages
-// (F, u) and reconstructs F +- alpha u with alpha the largest speed of the 2R
-// cells.
-template <class T, int ORDER>
-__device__ __forceinline__ T recon_local(const T* wa, const T* wb, T alpha, T eps2) {
-    constexpr int W = ORDER + 1;
-    T wp[W], wm[W];
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        wp[j] = wa[j] + alpha * wb[j];
-        wm[j] = wa[j] - alpha * wb[j];
-    }
-    return stage_recon_plus<T, ORDER>(wp, eps2) + stage_recon_minus<T, ORDER>(wm, eps2);
-}
 
 template <class T, int DIR, bool LOCAL>
 __device__ __forceinline__ void stage_pair(const T u[5], T v, T P, T a[5], T b[5]) {
