@@ -328,10 +328,12 @@ __device__ __forceinline__ void sweep_roll_body(const SweepArgs<T>& A, unsigned 
 }
 
 // Minimum resident 256-thread blocks per CU for the rolling sweeps (= waves per
-// SIMD); caps the register window so that enough waves hide load latency.
-template <class T, int ORDER>
+// SIMD); caps the register window so that enough waves hide load latency.  FP64
+// WENO7 fits two (246 registers, no spill); left to itself the fused x-y sweep took 392
+// and ran one: 256^3 step 5190 -> 4760 us.
+template <class T>
 struct RollMinBlocks {
-    static constexpr int value = sizeof(T) == 4 ? 3 : (ORDER == 5 ? 2 : 1);
+    static constexpr int value = sizeof(T) == 4 ? 3 : 2;
 };
 
 template <class T, int ORDER, int TX>
@@ -340,7 +342,7 @@ __global__ void __launch_bounds__(256) sweep_x(SweepArgs<T> A) {
 }
 
 template <class T, int ORDER, int DIR>
-__global__ void __launch_bounds__(256, (RollMinBlocks<T, ORDER>::value)) sweep_roll(SweepArgs<T> A) {
+__global__ void __launch_bounds__(256, (RollMinBlocks<T>::value)) sweep_roll(SweepArgs<T> A) {
     sweep_roll_body<T, ORDER, DIR>(A, blockIdx.x, blockIdx.y);
 }
 
@@ -396,7 +398,7 @@ __global__ void __launch_bounds__(256) sweep_x_batch(BatchArgs<T> B) {
 }
 
 template <class T, int ORDER, int DIR>
-__global__ void __launch_bounds__(256, (RollMinBlocks<T, ORDER>::value)) sweep_roll_batch(BatchArgs<T> B) {
+__global__ void __launch_bounds__(256, (RollMinBlocks<T>::value)) sweep_roll_batch(BatchArgs<T> B) {
     const int g = find_grid(B, DIR, blockIdx.x);
     const SweepArgs<T> A = grid_args(B, g, DIR);
     const int lb = blockIdx.x - B.grids[g].blk0[DIR];
@@ -648,7 +650,7 @@ static hipError_t launch_roll(SweepArgs<T> a, hipStream_t s) {
 // the x part plus the y part, summed in that order as in the split sweeps, so
 // the result is bitwise that of sweep_x followed by sweep_roll<1>.
 template <class T, int ORDER>
-__global__ void __launch_bounds__(256, (RollMinBlocks<T, ORDER>::value)) sweep_xy(SweepArgs<T> A, T inv_hx) {
+__global__ void __launch_bounds__(256, (RollMinBlocks<T>::value)) sweep_xy(SweepArgs<T> A, T inv_hx) {
     constexpr int R = (ORDER + 1) / 2, W = 2 * R;
     constexpr int D = R;                  // rows whose x part of L is pending (row k's slot is read before row k + R enters)
     __shared__ T sx[2][5][256 + 2 * R];   // x split fluxes of the current row, halo copies at both ends
