@@ -327,7 +327,12 @@ __device__ __forceinline__ void split_flux(const T u[5], T fp[5], T fm[5], unsig
 //   h0 = (E1 - 11/8 E2)^2 + c E2^2,  h1 = (E2 - 5/8 E3)^2 + c E3^2,
 //   h2 = (E4 - 11/8 E3)^2 + c E3^2,  c = 39/64
 // (the remainder is the least energy given the difference that two
-// neighbouring candidates share, so h1 and h2 have it in common, and c is the same for all), so
+// neighbouring candidates share, so h1 and h2 have it in common, and c is the same
+// for all).  FP64 evaluates these; FP32 keeps the expanded forms
+//   h0 = E1^2 - 11/4 E1 E2 + 5/2 E2^2,  h1 = E2^2 - 5/4 E2 E3 + E3^2,
+//   h2 = E4^2 - 11/4 E3 E4 + 5/2 E3^2,
+// one operation more (256^3 step 1870 against 1815 us), so that single-precision
+// runs keep their bits.  Then
 // g_k = (h_k + 3/16 (4 eps))^2 is (3/16)^2 (4 eps + 4 beta_k)^2 and the common
 // factor cancels in the weights
 // alpha_k = d_k / (eps + beta_k)^2, d = (1, 6, 3)/10, which are evaluated with
@@ -341,11 +346,18 @@ __device__ __forceinline__ T weno5(T s0, T s1, T s2, T s3, T s4, T eps4) {
     const T dq1s = E2 + (T)2 * E3;                              // 6 (q1 - c)
     const T dq2s = (T)2 * E3 - (T)0.5 * E4;                     // 3 (q2 - c)
     const T e = (T)0.1875 * eps4;
-    const T p2 = ((T)0.609375 * E2) * E2 + e, p3 = ((T)0.609375 * E3) * E3 + e;
-    const T a0 = E1 - (T)1.375 * E2, a1 = E2 - (T)0.625 * E3, a2 = E4 - (T)1.375 * E3;
-    T g0 = a0 * a0 + p2;
-    T g1 = a1 * a1 + p3;
-    T g2 = a2 * a2 + p3;
+    T g0, g1, g2;
+    if constexpr (sizeof(T) == 4) {
+        g0 = E1 * (E1 - (T)2.75 * E2) + ((T)2.5 * E2 * E2 + e);
+        g1 = E2 * (E2 - (T)1.25 * E3) + (E3 * E3 + e);
+        g2 = E4 * (E4 - (T)2.75 * E3) + ((T)2.5 * E3 * E3 + e);
+    } else {
+        const T p2 = ((T)0.609375 * E2) * E2 + e, p3 = ((T)0.609375 * E3) * E3 + e;
+        const T a0 = E1 - (T)1.375 * E2, a1 = E2 - (T)0.625 * E3, a2 = E4 - (T)1.375 * E3;
+        g0 = a0 * a0 + p2;
+        g1 = a1 * a1 + p3;
+        g2 = a2 * a2 + p3;
+    }
     g0 *= g0;
     g1 *= g1;
     g2 *= g2;
@@ -405,17 +417,35 @@ __device__ __forceinline__ T weno7(T s0, T s1, T s2, T s3, T s4, T s5, T s6, T e
     const T q1 = ((T)4 * D3 - D2) + (T)3 * D4;
     const T q2 = (T)1.5 * (D3 - D5) + (T)9 * D4;
     const T q3 = ((T)3 * D4 - (T)(4.0 / 3.0) * D5) + (T)(1.0 / 3.0) * D6;
-    const Smooth7<T> S = smooth7<T>(D1, D2, D3, D4, D5, D6, eps);
-    const T g0 = S.g0 * S.g0, g1 = S.g1 * S.g1, g2 = S.g2 * S.g2, g3 = S.g3 * S.g3;
     if constexpr (sizeof(T) == 8) {
         // FP64: one reciprocal, the weights multiplied through by g0 g1 g2 g3
+        const Smooth7<T> S = smooth7<T>(D1, D2, D3, D4, D5, D6, eps);
+        const T g0 = S.g0 * S.g0, g1 = S.g1 * S.g1, g2 = S.g2 * S.g2, g3 = S.g3 * S.g3;
         const T g01 = g0 * g1, g23 = g2 * g3;
         const T num = g23 * (g1 * q0 + g0 * q1) + g01 * (g3 * q2 + g2 * q3);
         const T den = g23 * (g1 + (T)12 * g0) + g01 * ((T)18 * g3 + (T)4 * g2);
         return s3 + num * fast_rcp(den);
     } else {
-        // FP32: products of three squared terms can overflow, so one reciprocal
-        // per weight
+        // FP32: 240 beta_k as quadratic forms in its three differences
+        // (x, y, z) = (D_{k+1}, D_{k+2}, D_{k+3}); the factor 240 (on eps too)
+        // cancels in the weights.  Rounding in the terms grows by at most the ratio
+        // of the summed absolute coefficients to 240 (68 for the outer stencils): a
+        // few 1e-6 relative in beta, far below the parity bar.  The completed
+        // squares take 12 operations less; the expanded forms stay so that
+        // single-precision runs keep their bits.
+        const T e = (T)240 * eps;
+        auto q = [e](T x, T y, T z, T cxx, T cxy, T cxz, T cyy, T cyz, T czz) {
+            return x * (cxx * x + cxy * y + cxz * z) + (y * (cyy * y + cyz * z) + (czz * z * z + e));
+        };
+        T g0 = q(D1, D2, D3, (T)547, (T)-2788, (T)1854, (T)3708, (T)-5188, (T)2107);
+        T g1 = q(D2, D3, D4, (T)267, (T)-1108, (T)494, (T)1468, (T)-1428, (T)547);
+        T g2 = q(D3, D4, D5, (T)547, (T)-1428, (T)494, (T)1468, (T)-1108, (T)267);
+        T g3 = q(D4, D5, D6, (T)2107, (T)-5188, (T)1854, (T)3708, (T)-2788, (T)547);
+        g0 *= g0;
+        g1 *= g1;
+        g2 *= g2;
+        g3 *= g3;
+        // products of three squared terms can overflow, so one reciprocal per weight
         const T r0 = fast_rcp(g0), r1 = fast_rcp(g1), r2 = fast_rcp(g2), r3 = fast_rcp(g3);
         const T num = (r0 * q0 + r1 * q1) + (r2 * q2 + r3 * q3);
         const T den = (r0 + (T)12 * r1) + ((T)18 * r2 + (T)4 * r3);
