@@ -194,12 +194,8 @@ void fill_stage_grid(rh::StageGrid<T>& g, const rh_grid_desc& d, long long off, 
     g.limiter = d.limiter;
     g.mk = d.musta_stages;
     g.lam = (T)d.musta_cfl;
-    if (d.scheme == RH_SCHEME_MUSTA) {
-        const int n[3] = {d.nx, d.ny, d.nz};
-        rh::musta_shape<T>(g, seg > 0 ? seg : rh::musta_default_segment(n));
-    } else {
-        rh::stage_shape<T>(g, tx, seg);
-    }
+    if (d.scheme == RH_SCHEME_MUSTA) rh::musta_shape<T>(g, seg);
+    else rh::stage_shape<T>(g, tx, seg);
 }
 
 // Descriptions resolved for the kernels: defaults of the optional fields filled in.
@@ -238,23 +234,23 @@ bool needs_recovery(const rh_grid_desc& d) { return d.eos == RH_EOS_IDEAL && d.s
 // Grids whose evaluations RH_PATH_AUTO gives to the fused stage (bitwise the
 // results of the sweeps).  One launch per stage instead of three, with as many
 // blocks as the chip takes, wins wherever latency or the L accumulator's traffic
-// counts: 31 against 135 us per FP32 WENO5 step at 33 x 20 x 17, 61 against 232 at
-// 64^3, 430 against 500 at 203 x 150 x 97, 1950 against 2240 at 256^3 with outflow
-// boundaries.  The sweeps are kept
-//   - for WENO5 where the fused x-y sweep applies to large grids (256^3 periodic:
-//     1855 against 1955 us FP32, 3675 against 3750 FP64; 128^3 FP32: 300 against 316;
-//     192 lanes per row leave it behind, 860 against 840),
+// counts: 31 against 135 us per FP32 WENO5 step at 33 x 20 x 17, 60 against 232 at
+// 64^3, 425 against 500 at 203 x 150 x 97, 275 against 294 at 128^3, 1970 against
+// 2260 at 256^3 with outflow boundaries.  The sweeps are kept
+//   - for WENO5 where the fused x-y sweep takes large grids in full rows (256^3
+//     periodic: 1870 against 1970 us FP32, 3520 against 3500 FP64; rows of 192 leave
+//     it behind, 865 against 844),
 //   - for WENO7 from the size where the stage's fewer waves (two per SIMD in FP32,
-//     one in FP64) cost more than its traffic saves (FP32: 276 against 357 us at
-//     96^3, 521 against 515 at 128^3; FP64: 147 against 472 at 64^3, 506 against 477
-//     at 96^3, 8190 against 6600 at 256^3).
+//     one in FP64) cost more than its traffic saves (FP32: 244 against 350 us at
+//     96^3, 519 against 509 at 128^3; FP64: 354 against 370 at 96^3, 781 against 690
+//     at 128^3, 6290 against 4760 at 256^3).
 bool auto_stage(const rh_grid_desc& d) {
     if (d.nx < 2 || d.ny < 2 || d.nz < 2) return false;
     const long long cells = (long long)d.nx * d.ny * d.nz;
     const bool fp32 = d.precision == RH_PREC_FP32;
-    if (d.scheme == 7) return cells < (fp32 ? 2000000 : 500000);
+    if (d.scheme == 7) return cells < (fp32 ? 2000000 : 1200000);
     const int n[3] = {d.nx, d.ny, d.nz};
-    const bool rows = d.nx % 128 == 0 && rh::sweep_xy_applies(5, fp32 ? 4 : 8, n, d.bc[0]);
+    const bool rows = d.nx == 256 && rh::sweep_xy_applies(5, fp32 ? 4 : 8, n, d.bc[0]);
     return !(rows && cells >= 2000000);
 }
 
@@ -269,7 +265,6 @@ bool use_stage(const rh_plan* p) {
 int plan_stage_segment(const rh_plan* p) {
     if (p->stage_seg > 0) return p->stage_seg;
     const int n[3] = {p->d.nx, p->d.ny, p->d.nz};
-    if (p->d.scheme == RH_SCHEME_MUSTA) return rh::musta_default_segment(n);
     return rh::stage_segment(1, &n, p->stage_tx, p->d.scheme, (int)p->elem, p->d.flux_split == RH_SPLIT_LOCAL);
 }
 
@@ -1167,16 +1162,14 @@ rh_status rh_batch_create(rh_batch** out, int n_grids, const rh_grid_desc* descs
             b->tile_x = tx;
         }
     }
-    if (b->scheme != RH_SCHEME_MUSTA) {
-        std::vector<int> n(3 * (size_t)n_grids);
-        for (int i = 0; i < n_grids; ++i) {
-            n[3 * i] = b->d[i].nx;
-            n[3 * i + 1] = b->d[i].ny;
-            n[3 * i + 2] = b->d[i].nz;
-        }
-        b->stage_seg = rh::stage_segment(n_grids, (const int (*)[3])n.data(), b->stage_tx, b->scheme, (int)b->elem,
-                                         b->d[0].flux_split == RH_SPLIT_LOCAL);
+    std::vector<int> n(3 * (size_t)n_grids);
+    for (int i = 0; i < n_grids; ++i) {
+        n[3 * i] = b->d[i].nx;
+        n[3 * i + 1] = b->d[i].ny;
+        n[3 * i + 2] = b->d[i].nz;
     }
+    b->stage_seg = rh::stage_segment(n_grids, (const int (*)[3])n.data(), b->stage_tx, b->scheme, (int)b->elem,
+                                     b->d[0].flux_split == RH_SPLIT_LOCAL);
     hipError_t e;
     if ((e = hipMalloc(&b->d_clamps, sizeof(unsigned))) != hipSuccess ||
         (e = hipMalloc(&b->d_partials, 6 * rh::kTotalsBlocks * sizeof(double))) != hipSuccess ||

@@ -203,9 +203,9 @@ long long stage_blocks(const StageGrid<T>& g) {
 template <class T>
 hipError_t launch_stage(int order, int tx, bool hub, bool local, int eos, const StageArgs<T>& a,
                         long long nblocks, hipStream_t s);
-// z segment of the fused stage for a launch over ngrid grids of n[g] cells (tiles
-// of tx, elem bytes per value).
-int stage_segment(int ngrid, const int (*n)[3], int tx, int order, int elem, bool local);
+// z segment of the stage kernels for a launch over ngrid grids of n[g] cells
+// (scheme 5, 7 or RH_SCHEME_MUSTA; tiles of tx, elem bytes per value).
+int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bool local);
 
 // MUSTA-FORCE stage (the same work items, with x-y tiles of kMustaTX x
 // kMustaTY cells): one launch evaluates the MUSCL + MUSTA face fluxes of x, y
@@ -213,7 +213,6 @@ int stage_segment(int ngrid, const int (*n)[3], int tx, int order, int elem, boo
 constexpr int kMustaTX = 16, kMustaTY = 15;
 template <class T>
 void musta_shape(StageGrid<T>& g, int seg);
-int musta_default_segment(const int n[3]);
 template <class T>
 // limiter (RH_LIMITER_*) and mk (FORCE evaluations per face) are those of
 // every grid of the launch (they select the kernel instance).

@@ -234,20 +234,6 @@ __global__ void __launch_bounds__(256, (MustaMinBlocks<T>::value)) stage_musta(S
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-int musta_default_segment(const int n[3]) {
-    // about 4096 blocks (several resident blocks per CU on 256 CUs), segments
-    // of 8 to 64 planes (each segment re-enters 2G = 4 halo planes)
-    const long long tiles = (long long)((n[0] + TX - 1) / TX) * ((n[1] + TY - 1) / TY);
-    const long long target = 4096;
-    long long nseg = (target + tiles - 1) / tiles;
-    const long long max_seg = (n[2] + 7) / 8;
-    if (nseg > max_seg) nseg = max_seg;
-    if (nseg < 1) nseg = 1;
-    int seg = (int)((n[2] + nseg - 1) / nseg);
-    if (seg > 64) seg = 64;
-    return seg;
-}
-
 template <class T>
 void musta_shape(StageGrid<T>& g, int seg) {
     if (seg < 1) seg = 1;

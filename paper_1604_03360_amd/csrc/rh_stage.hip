@@ -532,22 +532,34 @@ template hipError_t launch_recover_ideal<double>(const StageArgs<double>&, long 
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-// z segment of the fused stage for the grids of a launch: the length with the
-// least estimated time, in units of one plane of a block that has its CU to
-// itself.  Such a block takes 1 + seg (the window fill costs about one plane);
-// with every resident slot of a CU taken, a block costs q (0.6 + seg).  Fitted
-// to 16^3 .. 256^3 at seg 1 .. 64 (FP32 WENO5: 10.0 us at seg 1 and 86 us at seg
-// 16 alone, 3.9 and 40 us per block with the chip full); the choices are within
-// 5% of the best measured segment.  Small grids get segments of one plane (16^3
-// FP32: 30 us per step, 258 us with one segment of 16), 256^3 gets 16 to 32.
-int stage_segment(int ngrid, const int (*n)[3], int tx, int order, int elem, bool local) {
-    const int ty = 256 / tx;
-    const bool light = order == 5 && !local;
-    const int occ = elem == 4 ? (light ? 3 : 2) : (light && tx == 16 ? 2 : 1);
-    const double q = elem == 4 ? (light ? 0.46 : 0.62) : (light ? 0.74 : 1.05);
+// z segment of the stage kernels (fused WENO and MUSTA-FORCE) for the grids of a
+// launch: the length with the least estimated time, in units of one plane of a block that has its CU to
+// itself.  Such a block takes 1 + seg (its fill costs about one plane); occ blocks
+// share a CU and then take occ q (0.6 + seg) together, and part of them a time in
+// between.  Every length is tried: what a few planes more cost counts less than
+// whether the last blocks leave the chip idle (96^3 FP64 WENO5: 214 us per step at 7
+// planes, 504 blocks on 512 slots; 267 at 6, 233 at 8).  Against all segments measured
+// for 64^3 .. 160^3, both orders and precisions, and MUSTA-FORCE for 24^3 .. 256^3, the
+// choices are within 2% of the best (MUSTA-FORCE 5%).  Before, MUSTA-FORCE took segments
+// of at least 8 planes: 24^3 172 us per FP32 step, now 36; 128^3 FP64 611, now 559.
+int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bool local) {
+    const bool musta = scheme == RH_SCHEME_MUSTA, light = scheme == 5 && !local;
+    const int ty = musta ? kMustaTY : 256 / tx;
+    int occ;
+    double q;
+    if (musta) {
+        occ = elem == 4 ? 3 : 2;
+        q = elem == 4 ? 0.51 : 0.70;
+    } else if (elem == 4) {
+        occ = light ? 3 : 2;
+        q = light ? 0.46 : 0.62;
+    } else {
+        occ = light && tx == 16 ? 2 : 1;
+        q = occ == 2 ? 0.74 : 1.05;
+    }
     int best = 1;
     double best_t = 1e300;
-    for (int seg : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
+    for (int seg = 1; seg <= 64; ++seg) {
         long long blocks = 0;
         int planes = 1;
         for (int g = 0; g < ngrid; ++g) {
@@ -555,15 +567,15 @@ int stage_segment(int ngrid, const int (*n)[3], int tx, int order, int elem, boo
             blocks += (long long)((n[g][0] + tx - 1) / tx) * ((n[g][1] + ty - 1) / ty) * nseg;
             if (n[g][2] > planes) planes = n[g][2];
         }
-        const double alone = 1.0 + (seg < planes ? seg : planes), full = q * (0.6 + seg);
-        const long long per_cu = (blocks + 255) / 256;
-        const double round = occ * full > alone ? occ * full : alone;
-        const double rest = (per_cu % occ) * full;
-        const double t = (per_cu / occ) * round + (per_cu % occ ? (rest > alone ? rest : alone) : 0.0);
+        const double alone = 1.0 + (seg < planes ? seg : planes), all = occ * q * (0.6 + seg);
+        const long long per_cu = (blocks + 255) / 256, rest = per_cu % occ;
+        double t = (per_cu / occ) * (all > alone ? all : alone);
+        if (rest) t += occ > 1 ? alone * (1.0 + (occ * q - 1.0) * (rest - 1) / (occ - 1)) : alone;
         if (t < best_t * (1.0 - 1e-9)) {
             best_t = t;
             best = seg;
         }
+        if (seg >= planes) break;
     }
     return best;
 }
