@@ -19,7 +19,7 @@
 // 1.94 ms per FP32 WENO5 step and 3.98 against 3.63 ms in FP64 at 256^3, and 34.6
 // against 30.0 us at 16^3.  The window's 2R planes are loaded before the first
 // is recovered, so that a segment of one plane waits for memory once.  What bounds
-// it: VALU issue where the chip is full (FP32: three waves per SIMD, 156
+// it: VALU issue where the chip is full (FP32: three waves per SIMD, 165
 // registers; capped at 128 registers for a fourth, the spills cost 14%); the dependent chains of
 // recovery and reconstruction of one plane (about 5 us) where it is not.
 //
@@ -44,12 +44,15 @@
 
 namespace rh {
 
-// Minimum resident blocks per CU (= waves per SIMD) for the register budget;
-// FP64 blocks other than WENO5 16 x 16 with global splitting need more than
-// half of the 160 KB LDS.
-template <class T, int ORDER, int TX, bool LOCAL>
+// Minimum resident blocks per CU (= waves per SIMD) for the register budget.  FP32
+// WENO5 runs three waves (local splitting too: 174 registers for two, 192^3 step 1256
+// us; 168 for three, 1141), except where analytic ghosts and local splitting together
+// would spill 41 registers.  FP64 blocks other than WENO5 16 x 16 with global
+// splitting need more than half of the 160 KB LDS.
+template <class T, int ORDER, int TX, bool HUB, bool LOCAL>
 struct StageMinBlocks {
-    static constexpr int value = sizeof(T) == 4 ? (ORDER == 5 && !LOCAL ? 3 : 2) : (ORDER == 5 && TX == 16 && !LOCAL ? 2 : 1);
+    static constexpr int value = sizeof(T) == 4 ? (ORDER == 5 && !(HUB && LOCAL) ? 3 : 2)
+                                                : (ORDER == 5 && TX == 16 && !LOCAL ? 2 : 1);
 };
 
 template <class T, int DIR, bool LOCAL>
@@ -68,7 +71,7 @@ __device__ __forceinline__ void stage_pair(const T u[5], T v, T P, T a[5], T b[5
 }
 
 template <class T, int ORDER, int TX, bool HUB, bool LOCAL, int EOS>
-__global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::value)) stage_fused(StageArgs<T> A) {
+__global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>::value)) stage_fused(StageArgs<T> A) {
     constexpr int R = (ORDER + 1) / 2, W = 2 * R, TY = 256 / TX;
     static_assert(W * (TX + TY) <= 256, "one halo cell per lane and plane");
     static_assert(5 * (TX + TY) <= 256, "one edge face (all components) per lane");
@@ -127,27 +130,46 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
         hyc = y0 - R + hr;
     }
 
-    auto fetch_plane = [&](int k, T u[5]) {   // own cell of a plane of the grid
-        const uint32_t off = cb + (uint32_t)k * sb;
+    // The halo cell's place in a plane is the same every plane: its ghost index is
+    // taken once (per plane and cell: 53.9 against 52.6 us per step at 48^3 FP64).
+    // Analytic ghost cells load the edge cell like outflow ones and are replaced
+    // where they are used, so that the loads of the next plane stay in flight without
+    // the evaluation's registers (evaluated in place of the load, the loads of the
+    // next plane waited: 192^3 FP64 1670 against 1572 us, FP32 886 against 832).
+    const int hxi = hxc >= 0 && hxc < nx ? hxc : ghost_index(hxc, nx, G.bc[0]);
+    const int hyi = hyc >= 0 && hyc < ny ? hyc : ghost_index(hyc, ny, G.bc[1]);
+    const uint32_t hb = (uint32_t)sizeof(T) * ((uint32_t)hxi + (uint32_t)nx * (uint32_t)hyi);
+    const bool hana = HUB && hkind && ((G.bc[0] == RH_BC_HUBBLE && (hxc < 0 || hxc >= nx)) ||
+                                       (G.bc[1] == RH_BC_HUBBLE && (hyc < 0 || hyc >= ny)));
+    auto plane_of = [&](int m) { return m >= 0 && m < nz ? m : ghost_index(m, nz, G.bc[2]); };
+    auto load_at = [&](const T* base, uint32_t at, int k, T u[5]) {   // plane k of the grid
+        const uint32_t off = at + (uint32_t)k * sb;
 #pragma unroll
-        for (int f = 0; f < 5; ++f) u[f] = ld_off(us + f * F, off);
+        for (int f = 0; f < 5; ++f) u[f] = ld_off(base + f * F, off);
     };
-    auto fetch_own = [&](int m, T u[5]) {     // the same, or a ghost plane's
-        if (m >= 0 && m < nz) fetch_plane(m, u);
-        else stage_load<T, HUB>(G, us, F, t, cx, cy, m, u);
+    auto analytic = [&](int x, int y, int z, T u[5]) {
+        HubbleBC hbc;
+        hbc.t = t;
+        hbc.t0 = G.t0;
+        hbc.e0 = G.e0;
+        hbc.n0 = G.n0;
+        double uh[5];
+        hubble_conserved(hbc, G.c0[0] + x * G.h[0], G.c0[1] + y * G.h[1], G.c0[2] + z * G.h[2], uh);
+#pragma unroll
+        for (int f = 0; f < 5; ++f) u[f] = (T)uh[f];
     };
-    auto fetch_halo = [&](int m, T u[5]) {
-        if (hkind) stage_load<T, HUB>(G, us, F, t, hxc, hyc, m, u);
+    auto fetch_plane = [&](int k, T u[5]) { load_at(us, cb, k, u); };          // own cell of plane k
+    auto fetch_own = [&](int m, T u[5]) { load_at(us, cb, plane_of(m), u); };  // the same, or a ghost plane's
+    auto fetch_halo = [&](int k, T u[5]) {
+        if (hkind) load_at(us, hb, k, u);
     };
     // ideal gas: the recovery pass's (vx, vy, vz, p, c_s^2) of the same cells
     const T* pr = EOS == EOS_IDEAL ? A.prim + G.off : nullptr;
     auto fetch_own_prim = [&](int m, T q[5]) {
-        if constexpr (EOS == EOS_IDEAL) stage_load<T, false>(G, pr, F, t, cx, cy, m, q);
+        if constexpr (EOS == EOS_IDEAL) load_at(pr, cb, plane_of(m), q);
     };
-    auto fetch_halo_prim = [&](int m, T q[5]) {
-        if constexpr (EOS == EOS_IDEAL) {
-            if (hkind) stage_load<T, false>(G, pr, F, t, hxc, hyc, m, q);
-        }
+    auto fetch_halo_prim = [&](int k, T q[5]) {
+        if constexpr (EOS == EOS_IDEAL) load_at(pr, hb, k, q);
     };
 
     const T eps2 = (T)4 * G.eps;   // epsilon of the doubled split fluxes
@@ -158,7 +180,8 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
     T zsp[LOCAL ? W : 1];     // LOCAL: their largest speeds along z
 
     // z pair of a cell entering the window (and its largest speed along z)
-    auto z_pair = [&](int m, const T u[5], T fp[5], T fm[5], T& speed) {
+    auto z_pair = [&](int m, T u[5], T fp[5], T fm[5], T& speed) {
+        if (HUB && G.bc[2] == RH_BC_HUBBLE && (m < 0 || m >= nz)) analytic(cx, cy, m, u);
         T VZ, P;
         if constexpr (EOS == EOS_IDEAL) {
             T q[5];
@@ -189,7 +212,7 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
 
     // Stage the x and y pairs of the own cell of plane k and of the lane's halo
     // cell in LDS.
-    auto stage_xy = [&](int k, const T u[5], const T hu[5]) {
+    auto stage_xy = [&](int k, const T u[5], T hu[5]) {
         T fp[5], fm[5];
         if (act) {
             T VX, VY, P;
@@ -242,6 +265,7 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
                 ssy[R + ly][lx] = (T)max_char_speed(vyd, v2, cs2);
             }
         }
+        if (HUB && hana) analytic(hxc, hyc, k, hu);
         if (hkind) {
             T HX, HY, HP;
             double hxd, hyd, hv2 = 0.0, hcs2 = 0.0;
@@ -397,26 +421,17 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
             if constexpr (LOCAL) zsp[j] = sz;
         }
     }
-    // operands of the next plane, in flight during this one; with analytic ghost
-    // cells the window's next plane only (all three spill: 128^3 FP64 551 us per
-    // step against 531, FP32 368 against 350)
-    constexpr bool AHEAD = !HUB;
+    // operands of the next plane, in flight during this one
     T nz5[5], no5[5], nh5[5] = {(T)0, (T)0, (T)0, (T)0, (T)0};
     fetch_own(k0 + R, nz5);
-    if constexpr (AHEAD) {
-        fetch_plane(k0, no5);
-        fetch_halo(k0, nh5);
-    }
+    fetch_plane(k0, no5);
+    fetch_halo(k0, nh5);
     T Fl[5];
 #pragma unroll
     for (int c = 0; c < 5; ++c) Fl[c] = zface(c);
 
     for (int k = k0; k < kend; ++k) {
         T uz[5], u[5];
-        if constexpr (!AHEAD) {
-            fetch_plane(k, no5);
-            fetch_halo(k, nh5);
-        }
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
             uz[f] = nz5[f];
@@ -425,10 +440,8 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, LOCAL>::val
         stage_xy(k, u, nh5);
         if (k + 1 < kend) {
             fetch_own(k + 1 + R, nz5);
-            if constexpr (AHEAD) {
-                fetch_plane(k + 1, no5);
-                fetch_halo(k + 1, nh5);
-            }
+            fetch_plane(k + 1, no5);
+            fetch_halo(k + 1, nh5);
         }
         {
             T fp[5], fm[5], sz = (T)0;
@@ -543,7 +556,7 @@ template hipError_t launch_recover_ideal<double>(const StageArgs<double>&, long 
 // choices are within 2% of the best (MUSTA-FORCE 5%).  Before, MUSTA-FORCE took segments
 // of at least 8 planes: 24^3 172 us per FP32 step, now 36; 128^3 FP64 611, now 559.
 int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bool local) {
-    const bool musta = scheme == RH_SCHEME_MUSTA, light = scheme == 5 && !local;
+    const bool musta = scheme == RH_SCHEME_MUSTA, light = scheme == 5 && (elem == 4 || !local);
     const int ty = musta ? kMustaTY : 256 / tx;
     int occ;
     double q;
