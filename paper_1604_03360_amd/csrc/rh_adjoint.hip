@@ -2,13 +2,14 @@
 //
 // One adjoint sweep per axis, all reading a per-cell pack of the primitive
 // recovery and its derivatives (FP64 arithmetic).  The x sweep stages
-// contiguous rows in LDS, differentiates each face once and gathers the face
+// contiguous cells in LDS, differentiates each face once and gathers the face
 // partials per cell; it writes the output from the caller's linear combination
 // plus its part.  On periodic rows of 32..256 cells it takes whole rows
-// (adj_xrow) and also computes and stores the pack; otherwise it takes tiles
-// (adj_tile) after a separate pack launch (adj_pack).  The y and z sweeps of small
-// grids take tiles as well; those of large grids (adj_roll)
-// give each lane a segment [k0, k1) of one grid line; the lane rolls along it
+// (adj_xrow) and also computes and stores the pack; otherwise it takes short tiles
+// that recover for themselves (adj_small) or, in FP32 WENO5 on large grids, longer
+// ones that read the pack (adj_x); a launch of its own (adj_pack) then fills the
+// pack.  Small grids take adj_small along every axis and need no pack.  The y and
+// z sweeps of large grids (adj_roll) give each lane a segment [k0, k1) of one grid line; the lane rolls along it
 // over every face whose stencil reaches an owned position (the segment plus R
 // faces on each side), keeping a register window of 2R cells of split fluxes
 // and of split-flux adjoints; for each face it adds the face weight
@@ -468,40 +469,246 @@ __global__ void adj_pack(const T* __restrict__ u, T* __restrict__ pk, long long 
 }
 
 // ---------------------------------------------------------------------------
-// Tiles: a block takes a tile of TX positions along the axis x TY lines plus
-// ghosts in LDS.  Per component, each lane differentiates one face (the tile's
-// faces are spread over the lanes) and writes the face's stencil partials to LDS;
-// after a barrier each lane sums the partials of the faces that reach its cell
-// in a fixed order.  With all five split-flux adjoints of its cell in registers
-// the lane applies the flux Jacobian once.  The x axis writes out = (linear
-// combination of init terms) + scale g; y and z add scale g to out.
+// x axis of large grids, FP32 WENO5: x is contiguous, so a block takes a tile of TX cells x TY rows plus
+// ghosts in LDS, as the forward x sweep does.  Per component, each lane
+// differentiates one face (the tile's faces are spread over the lanes) and
+// writes the face's stencil partials to LDS; after a barrier each lane sums
+// the partials of the faces that reach its cell in a fixed order.  With all
+// five split-flux adjoints of its cell in registers the lane applies the flux
+// Jacobian once and writes out = (linear combination of init terms) + scale g.
 // Outflow ghost positions fold onto the edge cells (same state, so their
 // split-flux adjoints add before the Jacobian); analytic ghosts are constants.
-//
-// Lines are numbered so that consecutive ones are neighbours in memory: along x
-// a line is a row and lanes run along it, along y and z the lanes of a wave run
-// across the lines (x fastest), so every access is contiguous either way and the
-// LDS layout follows the lanes.
 // ---------------------------------------------------------------------------
-// First cell of line `p` of the axis DIR and the step between its cells.
-template <int DIR>
-__device__ __forceinline__ long long line_cell(const int n[3], int p, int m) {
-    if constexpr (DIR == 0) return m + (long long)n[0] * p;
-    else if constexpr (DIR == 1) return p % n[0] + (long long)n[0] * (m + (long long)n[1] * (p / n[0]));
-    else return p + (long long)n[0] * n[1] * m;
+template <class T>
+__device__ __forceinline__ void x_state(const AdjArgs<T>& A, int gx, int row, T u[5], T& v, T& P) {
+    const int nx = A.n[0];
+    int mx = gx;
+    if (gx < 0 || gx >= nx) {
+        if (A.bc == RH_BC_PERIODIC) {
+            mx = gx % nx;
+            if (mx < 0) mx += nx;
+        } else if (A.bc == RH_BC_OUTFLOW) {
+            mx = gx < 0 ? 0 : nx - 1;
+        } else {
+            const int y = row % A.n[1], z = row / A.n[1];
+            double uh[5];
+            hubble_conserved(A.hb, A.hb.c0[0] + gx * A.hb.h[0], A.hb.c0[1] + y * A.hb.h[1],
+                             A.hb.c0[2] + z * A.hb.h[2], uh);
+#pragma unroll
+            for (int f = 0; f < 5; ++f) u[f] = (T)uh[f];
+            double vd, pd;
+            unsigned dummy = 0;
+            recover_vp<0>(uh[0], uh[1], uh[2], uh[3], vd, pd, dummy);
+            v = (T)vd;
+            P = (T)pd;
+            return;
+        }
+    }
+    const long long id = mx + (long long)nx * row;
+#pragma unroll
+    for (int f = 0; f < 5; ++f) u[f] = A.u[f * A.fstride + id];
+    v = A.pk[id] * u[1];
+    P = A.pk[A.fstride + id];
 }
 
-// State, velocity along the axis and pressure at position m of a line.
+template <class T, int TX, int TY>
+__global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
+    constexpr int R = 3, K = 2 * R - 1;
+    constexpr int CPL = TX * TY / 256;   // cells per lane
+    constexpr int NF = TX + 2 * R - 1;   // faces x0-R .. x0+TX+R-2 (face i: between cells i and i+1)
+    constexpr int NC = TX + 4 * R - 2;   // cells x0-2R+1 .. x0+TX+2R-2
+    constexpr int NW = TX + 2 * R;       // weights x0-R .. x0+TX+R-1
+    static_assert(TX * TY % 256 == 0, "whole cells per lane");
+    __shared__ T sfp[5][TY][NC];
+    __shared__ T sfm[5][TY][NC];
+    __shared__ T sw[5][TY][NW];
+    __shared__ T sp[TY][NF][K];          // plus partials of face fl for cells fl .. fl+K-1 (local)
+    __shared__ T sm[TY][NF][K];          // minus partials of face fl for cells fl+1 .. fl+K
+    const int nx = A.n[0];
+    const int nrows = A.n[1] * A.n[2];
+    const int ntx = (nx + TX - 1) / TX;
+    const int bx = blockIdx.x % ntx, by = blockIdx.x / ntx;
+    const int x0 = bx * TX, r0 = by * TY;
+    const int tid = threadIdx.x;
+    const bool periodic = A.bc == RH_BC_PERIODIC;
+    const T half = (T)0.5;
+
+    for (int idx = tid; idx < TY * NC; idx += 256) {
+        const int ly = idx / NC, lx = idx - ly * NC;
+        const int row = r0 + ly;
+        T fp[5] = {(T)0, (T)0, (T)0, (T)0, (T)0}, fm[5] = {(T)0, (T)0, (T)0, (T)0, (T)0};
+        if (row < nrows) {
+            T u[5], v, P;
+            x_state<T>(A, x0 - 2 * R + 1 + lx, row, u, v, P);
+            T f[5];
+            f[0] = u[1];
+            f[1] = u[1] * v + P;
+            f[2] = u[2] * v;
+            f[3] = u[3] * v;
+            f[4] = u[4] * v;
+#pragma unroll
+            for (int c = 0; c < 5; ++c) {
+                fp[c] = f[c] + u[c];   // doubled split fluxes (eps scaled by 4 below)
+                fm[c] = f[c] - u[c];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+            sfp[c][ly][lx] = fp[c];
+            sfm[c][ly][lx] = fm[c];
+        }
+    }
+    for (int idx = tid; idx < TY * NW; idx += 256) {
+        const int ly = idx / NW, lx = idx - ly * NW;
+        const int row = r0 + ly;
+        int gx = x0 - R + lx;
+        bool inside = row < nrows;
+        if (inside && (gx < 0 || gx >= nx)) {
+            if (periodic) {
+                gx %= nx;
+                if (gx < 0) gx += nx;
+            } else {
+                inside = false;   // weights vanish outside a non-periodic grid
+            }
+        }
+        const long long id = gx + (long long)nx * row;
+#pragma unroll
+        for (int c = 0; c < 5; ++c) sw[c][ly][lx] = inside ? A.w[c * A.fstride + id] : (T)0;
+    }
+    __syncthreads();
+
+    T ap[CPL][5], am[CPL][5];
+#pragma unroll 1
+    for (int c = 0; c < 5; ++c) {
+        for (int f = tid; f < TY * NF; f += 256) {
+            const int fy = f / NF, fl = f - fy * NF;
+            const int i = x0 - R + fl;
+            T op[K], om[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) op[k] = om[k] = (T)0;
+            if ((periodic || (i >= -1 && i <= nx - 1)) && r0 + fy < nrows) {
+                const T g = (sw[c][fy][fl + 1] - sw[c][fy][fl]) * A.inv_h;
+                weno5_grad_acc_e<T>(sfp[c][fy][fl], sfp[c][fy][fl + 1], sfp[c][fy][fl + 2], sfp[c][fy][fl + 3],
+                                    sfp[c][fy][fl + 4], (T)16 * A.eps, g, op[0], op[1], op[2], op[3], op[4]);
+                weno5_grad_acc_e<T>(sfm[c][fy][fl + 5], sfm[c][fy][fl + 4], sfm[c][fy][fl + 3], sfm[c][fy][fl + 2],
+                                    sfm[c][fy][fl + 1], (T)16 * A.eps, g, om[4], om[3], om[2], om[1], om[0]);
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                sp[fy][fl][k] = op[k];
+                sm[fy][fl][k] = om[k];
+            }
+        }
+        __syncthreads();
+        // partials reaching staged cell q: plus from faces q-k, minus from faces q-1-k
+#pragma unroll
+        for (int j = 0; j < CPL; ++j) {
+            const int cell = tid + 256 * j, lx = cell % TX, ly = cell / TX;
+            const int q = lx + 2 * R - 1;   // every face reaching an owned cell is in the tile
+            T a_p = (T)0, a_m = (T)0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                a_p += sp[ly][q - k][k];
+                a_m += sm[ly][q - 1 - k][k];
+            }
+            const int gx = x0 + lx;
+            if (A.bc == RH_BC_OUTFLOW && (gx == 0 || gx == nx - 1) && r0 + ly < nrows) {
+                // ghost positions beyond the edge fold onto the edge cell
+                for (int e = 1; e < 2 * R; ++e) {
+                    const int qe = gx == 0 ? q - e : q + e;
+                    for (int k = 0; k < K; ++k) {
+                        const int fp_ = qe - k, fm_ = qe - 1 - k;
+                        if (fp_ >= 0 && fp_ < NF) a_p += sp[ly][fp_][k];
+                        if (fm_ >= 0 && fm_ < NF) a_m += sm[ly][fm_][k];
+                    }
+                }
+            }
+            ap[j][c] = a_p;
+            am[j][c] = a_m;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+        const int cell = tid + 256 * j, lx = cell % TX, ly = cell / TX;
+        const int gx = x0 + lx, row = r0 + ly;
+        if (gx >= nx || row >= nrows) continue;
+        const long long id = gx + (long long)nx * row;
+        T uf[5];
+#pragma unroll
+        for (int f = 0; f < 5; ++f) uf[f] = A.u[f * A.fstride + id];
+        const T kap = A.pk[id], kE = A.pk[2 * A.fstride + id], kM2 = A.pk[3 * A.fstride + id];
+        const T pE = A.pk[4 * A.fstride + id], pM2 = A.pk[5 * A.fstride + id];
+        T lam[5], g[5];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+            lam[c] = half * (ap[j][c] + am[j][c]);
+            g[c] = half * (ap[j][c] - am[j][c]);
+        }
+        // F = (Mx, Mx v + p, My v, Mz v, N v) with v = kappa Mx
+        const T Mx = uf[1], vd = kap * Mx;
+        g[1] += lam[0];
+        T S = (T)0;
+#pragma unroll
+        for (int c = 1; c < 5; ++c) {
+            S += lam[c] * uf[c];
+            g[c] += lam[c] * vd;
+        }
+        const T lp = lam[1];
+        g[0] += S * (Mx * kE) + lp * pE;
+        const T sk = (T)2 * S * Mx * kM2, spp = (T)2 * lp * pM2;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) g[1 + m] += (sk + spp) * uf[1 + m];
+        g[1] += S * kap;
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+            const long long o = f * A.fstride + id;
+            T acc = (T)0;
+            if (init.X1) acc += init.a1 * init.X1[o];
+            if (init.X2) acc += init.a2 * init.X2[o];
+            if (init.X3) acc += init.a3 * init.X3[o];
+            A.ub[o] = acc + A.scale * g[f];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Small grids along any axis, and x wherever whole rows do not fit: what bounds a
+// tile is the length of its chain of dependent work and its barriers (an FP64
+// recovery, two WENO gradients per lane), not its throughput.  A block takes 16 positions
+// along the axis x 4 lines and differentiates the faces of all five components
+// at once, one (component, face) per lane; the partials go to LDS, are gathered
+// one (component, cell) per lane, and the lane that owns the cell applies the
+// flux Jacobian: three barriers in all (a component at a time as in adj_x: eleven).
+// Each block recovers the primitives of the cells it stages (FP64, as adj_pack):
+// reading them from a pack measured no faster (130x128x128 FP64 868 us against
+// 877) and costs small grids a launch.  J^T w at 33x20x17 FP64 WENO7: 168 us with
+// rolling lanes, 58 with tiles that take a component at a time, 21 with these.  x
+// writes out = (linear combination of init terms) +
+// scale g; y and z add scale g to out.  The order of every sum is that of adj_x.
+//
+// Lines are numbered so that consecutive ones are neighbours in memory along y
+// and z; along x a line is a row.
+// ---------------------------------------------------------------------------
+// Position m of line `line` of the axis DIR.
+template <int DIR>
+__device__ __forceinline__ long long line_cell(const int n[3], int line, int m) {
+    if constexpr (DIR == 0) return m + (long long)n[0] * line;
+    else if constexpr (DIR == 1) return line % n[0] + (long long)n[0] * (m + (long long)n[1] * (line / n[0]));
+    else return line + (long long)n[0] * n[1] * m;
+}
+
+// State, velocity along the axis and pressure at position m of a line (ghost
+// cells by the boundary condition of the axis), recovered here.
 template <class T, int DIR>
 __device__ __forceinline__ void line_state(const AdjArgs<T>& A, int m, int line, T u[5], T& v, T& P) {
     const int nd = A.n[DIR];
-    int mm = m;
     if (m < 0 || m >= nd) {
         if (A.bc == RH_BC_PERIODIC) {
-            mm = m % nd;
-            if (mm < 0) mm += nd;
+            m %= nd;
+            if (m < 0) m += nd;
         } else if (A.bc == RH_BC_OUTFLOW) {
-            mm = m < 0 ? 0 : nd - 1;
+            m = m < 0 ? 0 : nd - 1;
         } else {
             int c[3];
             if (DIR == 0) { c[0] = m; c[1] = line % A.n[1]; c[2] = line / A.n[1]; }
@@ -520,31 +727,30 @@ __device__ __forceinline__ void line_state(const AdjArgs<T>& A, int m, int line,
             return;
         }
     }
-    const long long id = line_cell<DIR>(A.n, line, mm);
+    const long long id = line_cell<DIR>(A.n, line, m);
 #pragma unroll
     for (int f = 0; f < 5; ++f) u[f] = A.u[f * A.fstride + id];
-    v = A.pk[id] * u[1 + DIR];
-    P = A.pk[A.fstride + id];
+    const RecoveryPack o = recovery_pack((double)u[0], (double)u[1], (double)u[2], (double)u[3]);
+    v = (T)o.kap * u[1 + DIR];
+    P = (T)o.p;
 }
 
-template <class T, int ORDER, int DIR, int TX, int TY>
-__global__ void __launch_bounds__(256) adj_tile(AdjArgs<T> A, Lin3<T> init) {
+constexpr int kSmallTX = 16, kSmallTY = 4, kSmallLanes = 512;
+
+template <class T, int ORDER, int DIR>
+__global__ void __launch_bounds__(kSmallLanes) adj_small(AdjArgs<T> A, Lin3<T> init) {
     constexpr int R = (ORDER + 1) / 2, K = 2 * R - 1;
-    constexpr int CPL = TX * TY / 256;   // cells per lane
+    constexpr int TX = kSmallTX, TY = kSmallTY, CELLS = TX * TY;
     constexpr int NF = TX + 2 * R - 1;   // faces x0-R .. x0+TX+R-2 (face i: between cells i and i+1)
     constexpr int NC = TX + 4 * R - 2;   // cells x0-2R+1 .. x0+TX+2R-2
     constexpr int NW = TX + 2 * R;       // weights x0-R .. x0+TX+R-1
-    static_assert(TX * TY % 256 == 0, "whole cells per lane");
-    constexpr bool ALONG = DIR == 0;     // lanes run along the line, else across the lines
-    // LDS strides of (position, line): the lanes' direction is the fast one
-    constexpr int CX = ALONG ? 1 : TY, CY = ALONG ? NC : 1, WY = ALONG ? NW : 1;
-    __shared__ T sfp[5][TY * NC];
-    __shared__ T sfm[5][TY * NC];
-    __shared__ T sw[5][TY * NW];
-    __shared__ T sp[TY * NF * K];        // plus partials of face fl for cells fl .. fl+K-1 (local)
-    __shared__ T sm[TY * NF * K];        // minus partials of face fl for cells fl+1 .. fl+K
-    // partials: x keeps a face's K values together, y and z a line's neighbours
-    auto part = [](int ly, int fl, int k) { return ALONG ? (ly * NF + fl) * K + k : (fl * K + k) * TY + ly; };
+    constexpr int W0 = 128, OWN0 = 256;  // first lanes staging weights and owning cells
+    static_assert(NC * TY <= W0 && W0 + NW * TY <= OWN0 && OWN0 + CELLS <= kSmallLanes, "lanes for every role");
+    static_assert(5 * NF * TY <= kSmallLanes, "one face and component per lane");
+    __shared__ T sfp[5][NC * TY], sfm[5][NC * TY];   // split fluxes, [position][line]
+    __shared__ T sw[5][NW * TY];                     // weights
+    __shared__ T sp[5][K][NF * TY], sm[5][K][NF * TY];   // partials of face f for cells f + k (minus: f + 1 + k)
+    __shared__ T sa[10][CELLS];                      // split-flux adjoints of the tile's cells
     const int nd = A.n[DIR];
     const int nlines = DIR == 0 ? A.n[1] * A.n[2] : DIR == 1 ? A.n[0] * A.n[2] : A.n[0] * A.n[1];
     const int ntx = (nd + TX - 1) / TX;
@@ -554,8 +760,15 @@ __global__ void __launch_bounds__(256) adj_tile(AdjArgs<T> A, Lin3<T> init) {
     const bool periodic = A.bc == RH_BC_PERIODIC;
     const T half = (T)0.5;
 
-    for (int idx = tid; idx < TY * NC; idx += 256) {
-        const int ly = ALONG ? idx / NC : idx % TY, lx = ALONG ? idx - ly * NC : idx / TY;
+    // this lane's own cell (lanes OWN0 ..): along x lanes run along the line
+    const int own = tid - OWN0;
+    const int ox = DIR == 0 ? own & (TX - 1) : own / TY, oy = DIR == 0 ? own / TX : own & (TY - 1);
+    const bool owner = own >= 0 && own < CELLS && x0 + ox < nd && r0 + oy < nlines;
+    T uf[5] = {(T)0, (T)0, (T)0, (T)0, (T)0}, base[5];
+    T kap = (T)0, kE = (T)0, kM2 = (T)0, pE = (T)0, pM2 = (T)0;
+    long long oid = 0;
+    if (tid < NC * TY) {
+        const int lx = DIR == 0 ? tid % NC : tid / TY, ly = DIR == 0 ? tid / NC : tid & (TY - 1);
         const int line = r0 + ly;
         T fp[5] = {(T)0, (T)0, (T)0, (T)0, (T)0}, fm[5] = {(T)0, (T)0, (T)0, (T)0, (T)0};
         if (line < nlines) {
@@ -565,12 +778,12 @@ __global__ void __launch_bounds__(256) adj_tile(AdjArgs<T> A, Lin3<T> init) {
         }
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
-            sfp[c][idx] = fp[c];
-            sfm[c][idx] = fm[c];
+            sfp[c][lx * TY + ly] = fp[c];
+            sfm[c][lx * TY + ly] = fm[c];
         }
-    }
-    for (int idx = tid; idx < TY * NW; idx += 256) {
-        const int ly = ALONG ? idx / NW : idx % TY, lx = ALONG ? idx - ly * NW : idx / TY;
+    } else if (tid >= W0 && tid < W0 + NW * TY) {
+        const int j = tid - W0;
+        const int lx = DIR == 0 ? j % NW : j / TY, ly = DIR == 0 ? j / NW : j & (TY - 1);
         const int line = r0 + ly;
         int gx = x0 - R + lx;
         bool inside = line < nlines;
@@ -584,132 +797,120 @@ __global__ void __launch_bounds__(256) adj_tile(AdjArgs<T> A, Lin3<T> init) {
         }
         const long long id = inside ? line_cell<DIR>(A.n, line, gx) : 0;
 #pragma unroll
-        for (int c = 0; c < 5; ++c) sw[c][idx] = inside ? A.w[c * A.fstride + id] : (T)0;
+        for (int c = 0; c < 5; ++c) sw[c][lx * TY + ly] = inside ? A.w[c * A.fstride + id] : (T)0;
+    } else if (owner) {
+        oid = line_cell<DIR>(A.n, r0 + oy, x0 + ox);
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+            const long long o = f * A.fstride + oid;
+            uf[f] = A.u[o];
+            base[f] = (T)0;
+            if constexpr (DIR == 0) {
+                if (init.X1) base[f] += init.a1 * init.X1[o];
+                if (init.X2) base[f] += init.a2 * init.X2[o];
+                if (init.X3) base[f] += init.a3 * init.X3[o];
+            } else {
+                base[f] = A.ub[o];
+            }
+        }
+        const RecoveryPack o = recovery_pack((double)uf[0], (double)uf[1], (double)uf[2], (double)uf[3]);
+        kap = (T)o.kap;
+        kE = (T)o.kap_E;
+        kM2 = (T)o.kap_M2;
+        pE = (T)o.p_E;
+        pM2 = (T)o.p_M2;
     }
     __syncthreads();
 
-    T ap[CPL][5], am[CPL][5];
-#pragma unroll 1
-    for (int c = 0; c < 5; ++c) {
-        for (int f = tid; f < TY * NF; f += 256) {
-            const int fy = ALONG ? f / NF : f % TY, fl = ALONG ? f - fy * NF : f / TY;
-            const int i = x0 - R + fl;
-            T op[K], om[K];
+    if (tid < 5 * NF * TY) {
+        const int c = tid / (NF * TY), j = tid - c * (NF * TY), fl = j / TY;
+        const int i = x0 - R + fl;
+        T op[K], om[K];
 #pragma unroll
-            for (int k = 0; k < K; ++k) op[k] = om[k] = (T)0;
-            if ((periodic || (i >= -1 && i <= nd - 1)) && r0 + fy < nlines) {
-                const T* wf = &sw[c][fl * CX + fy * WY];
-                const T* cp = &sfp[c][fl * CX + fy * CY];
-                const T* cm = &sfm[c][fl * CX + fy * CY];
-                const T g = (wf[CX] - wf[0]) * A.inv_h;
-                if constexpr (ORDER == 5) {
-                    weno5_grad_acc_e<T>(cp[0], cp[CX], cp[2 * CX], cp[3 * CX], cp[4 * CX], (T)16 * A.eps, g, op[0],
-                                        op[1], op[2], op[3], op[4]);
-                    weno5_grad_acc_e<T>(cm[5 * CX], cm[4 * CX], cm[3 * CX], cm[2 * CX], cm[CX], (T)16 * A.eps, g,
-                                        om[4], om[3], om[2], om[1], om[0]);
-                } else {
-                    T sv[7], o[7];
-#pragma unroll
-                    for (int j = 0; j < 7; ++j) {
-                        sv[j] = cp[j * CX];
-                        o[j] = (T)0;
-                    }
-                    weno7_grad_acc<T>(sv, (T)4 * A.eps, g, o);
-#pragma unroll
-                    for (int j = 0; j < 7; ++j) op[j] = o[j];
-#pragma unroll
-                    for (int j = 0; j < 7; ++j) {
-                        sv[j] = cm[(7 - j) * CX];
-                        o[j] = (T)0;
-                    }
-                    weno7_grad_acc<T>(sv, (T)4 * A.eps, g, o);
-#pragma unroll
-                    for (int j = 0; j < 7; ++j) om[6 - j] = o[j];
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                sp[part(fy, fl, k)] = op[k];
-                sm[part(fy, fl, k)] = om[k];
-            }
-        }
-        __syncthreads();
-        // partials reaching staged cell q: plus from faces q-k, minus from faces q-1-k
-#pragma unroll
-        for (int j = 0; j < CPL; ++j) {
-            const int cell = tid + 256 * j;
-            const int lx = ALONG ? cell % TX : cell / TY, ly = ALONG ? cell / TX : cell % TY;
-            const int q = lx + 2 * R - 1;   // every face reaching an owned cell is in the tile
-            T a_p = (T)0, a_m = (T)0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                a_p += sp[part(ly, q - k, k)];
-                a_m += sm[part(ly, q - 1 - k, k)];
-            }
-            const int gx = x0 + lx;
-            if (A.bc == RH_BC_OUTFLOW && (gx == 0 || gx == nd - 1) && r0 + ly < nlines) {
-                // ghost positions beyond the edge fold onto the edge cell
-                for (int e = 1; e < 2 * R; ++e) {
-                    const int qe = gx == 0 ? q - e : q + e;
-                    for (int k = 0; k < K; ++k) {
-                        const int fp_ = qe - k, fm_ = qe - 1 - k;
-                        if (fp_ >= 0 && fp_ < NF) a_p += sp[part(ly, fp_, k)];
-                        if (fm_ >= 0 && fm_ < NF) a_m += sm[part(ly, fm_, k)];
-                    }
-                }
-            }
-            ap[j][c] = a_p;
-            am[j][c] = a_m;
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int j = 0; j < CPL; ++j) {
-        const int cell = tid + 256 * j;
-        const int lx = ALONG ? cell % TX : cell / TY, ly = ALONG ? cell / TX : cell % TY;
-        const int gx = x0 + lx, line = r0 + ly;
-        if (gx >= nd || line >= nlines) continue;
-        const long long id = line_cell<DIR>(A.n, line, gx);
-        T uf[5];
-#pragma unroll
-        for (int f = 0; f < 5; ++f) uf[f] = A.u[f * A.fstride + id];
-        const T kap = A.pk[id], kE = A.pk[2 * A.fstride + id], kM2 = A.pk[3 * A.fstride + id];
-        const T pE = A.pk[4 * A.fstride + id], pM2 = A.pk[5 * A.fstride + id];
-        T lam[5], g[5];
-#pragma unroll
-        for (int c = 0; c < 5; ++c) {
-            lam[c] = half * (ap[j][c] + am[j][c]);
-            g[c] = half * (ap[j][c] - am[j][c]);
-        }
-        // F = (M_d, M v + p e_d, N v) with v = kappa M_d
-        const T Md = uf[1 + DIR], vd = kap * Md;
-        g[1 + DIR] += lam[0];
-        T S = (T)0;
-#pragma unroll
-        for (int c = 1; c < 5; ++c) {
-            S += lam[c] * uf[c];
-            g[c] += lam[c] * vd;
-        }
-        const T lp = lam[1 + DIR];
-        g[0] += S * (Md * kE) + lp * pE;
-        const T sk = (T)2 * S * Md * kM2, spp = (T)2 * lp * pM2;
-#pragma unroll
-        for (int m = 0; m < 3; ++m) g[1 + m] += (sk + spp) * uf[1 + m];
-        g[1 + DIR] += S * kap;
-#pragma unroll
-        for (int f = 0; f < 5; ++f) {
-            const long long o = f * A.fstride + id;
-            T acc = (T)0;
-            if constexpr (DIR == 0) {
-                if (init.X1) acc += init.a1 * init.X1[o];
-                if (init.X2) acc += init.a2 * init.X2[o];
-                if (init.X3) acc += init.a3 * init.X3[o];
+        for (int k = 0; k < K; ++k) op[k] = om[k] = (T)0;
+        if ((periodic || (i >= -1 && i <= nd - 1)) && r0 + (j & (TY - 1)) < nlines) {
+            const T* cp = &sfp[c][j];
+            const T* cm = &sfm[c][j];
+            const T g = (sw[c][j + TY] - sw[c][j]) * A.inv_h;
+            if constexpr (ORDER == 5) {
+                weno5_grad_acc_e<T>(cp[0], cp[TY], cp[2 * TY], cp[3 * TY], cp[4 * TY], (T)16 * A.eps, g, op[0], op[1],
+                                    op[2], op[3], op[4]);
+                weno5_grad_acc_e<T>(cm[5 * TY], cm[4 * TY], cm[3 * TY], cm[2 * TY], cm[TY], (T)16 * A.eps, g, om[4],
+                                    om[3], om[2], om[1], om[0]);
             } else {
-                acc = A.ub[o];
+                T sv[7], o[7];
+#pragma unroll
+                for (int q = 0; q < 7; ++q) sv[q] = cp[q * TY];
+                weno7_grad_acc<T>(sv, (T)4 * A.eps, g, op);
+#pragma unroll
+                for (int q = 0; q < 7; ++q) {
+                    sv[q] = cm[(7 - q) * TY];
+                    o[q] = (T)0;
+                }
+                weno7_grad_acc<T>(sv, (T)4 * A.eps, g, o);
+#pragma unroll
+                for (int q = 0; q < 7; ++q) om[6 - q] = o[q];
             }
-            A.ub[o] = acc + A.scale * g[f];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            sp[c][k][j] = op[k];
+            sm[c][k][j] = om[k];
         }
     }
+    __syncthreads();
+    // partials reaching staged cell q: plus from faces q-k, minus from faces q-1-k
+    if (tid < 5 * CELLS) {
+        const int c = tid / CELLS, cell = tid - c * CELLS, lx = cell / TY, ly = cell & (TY - 1);
+        const int q = lx + 2 * R - 1;   // every face reaching an owned cell is in the tile
+        T a_p = (T)0, a_m = (T)0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            a_p += sp[c][k][(q - k) * TY + ly];
+            a_m += sm[c][k][(q - 1 - k) * TY + ly];
+        }
+        const int gx = x0 + lx;
+        if (A.bc == RH_BC_OUTFLOW && (gx == 0 || gx == nd - 1)) {
+            // ghost positions beyond the edge fold onto the edge cell (same state, so
+            // their split-flux adjoints add before the Jacobian)
+            for (int e = 1; e < 2 * R; ++e) {
+                const int qe = gx == 0 ? q - e : q + e;
+                for (int k = 0; k < K; ++k) {
+                    const int fp_ = qe - k, fm_ = qe - 1 - k;
+                    if (fp_ >= 0 && fp_ < NF) a_p += sp[c][k][fp_ * TY + ly];
+                    if (fm_ >= 0 && fm_ < NF) a_m += sm[c][k][fm_ * TY + ly];
+                }
+            }
+        }
+        sa[c][cell] = a_p;
+        sa[5 + c][cell] = a_m;
+    }
+    __syncthreads();
+    if (!owner) return;
+    T lam[5], g[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+        const T ap = sa[c][ox * TY + oy], am = sa[5 + c][ox * TY + oy];
+        lam[c] = half * (ap + am);
+        g[c] = half * (ap - am);
+    }
+    // F = (M_d, M v + p e_d, N v) with v = kappa M_d
+    const T Md = uf[1 + DIR], vd = kap * Md;
+    g[1 + DIR] += lam[0];
+    T S = (T)0;
+#pragma unroll
+    for (int c = 1; c < 5; ++c) {
+        S += lam[c] * uf[c];
+        g[c] += lam[c] * vd;
+    }
+    const T lp = lam[1 + DIR];
+    g[0] += S * (Md * kE) + lp * pE;
+    const T sk = (T)2 * S * Md * kM2, spp = (T)2 * lp * pM2;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) g[1 + m] += (sk + spp) * uf[1 + m];
+    g[1 + DIR] += S * kap;
+#pragma unroll
+    for (int f = 0; f < 5; ++f) A.ub[f * A.fstride + oid] = base[f] + A.scale * g[f];
 }
 
 // ---------------------------------------------------------------------------
@@ -720,7 +921,7 @@ __global__ void __launch_bounds__(256) adj_tile(AdjArgs<T> A, Lin3<T> init) {
 // and gathers the partials of the faces that reach its cell.  No lane stages a
 // ghost from HBM or differentiates a halo face, which the tiled kernel does for
 // 2R - 1 faces per row (a fifth of its face rounds at 64 x 4).  The arithmetic
-// and the order of every sum are those of adj_tile, so both give the same bits.
+// and the order of every sum are those of adj_x, so both give the same bits.
 // ---------------------------------------------------------------------------
 // FP32 WENO5 rows: six waves per SIMD, the most that the LDS of 256-cell row
 // blocks allows (62 registers instead of 82; 0.5% faster at 256^3).
@@ -945,14 +1146,20 @@ static unsigned blocks_for(long long n) {
     return (unsigned)b;
 }
 
-// Grids whose y and z adjoint take tiles.  A rolling lane differentiates every
-// face that reaches its segment, 2R - 1 more than it owns, one after another; a
-// tile differentiates each face once (and those of its ghosts) with all lanes,
-// but pays ten barriers and its staging.  Measured for J^T w, tiles against rolls
-// at their best segment: 40 x 36 x 28 FP64 WENO7 60 against 134 us (219 at segments of
-// 16), 64^3 FP32 WENO5 62 against 64, FP64 WENO7 124 against 145; 96^3 161 against
-// 138 and 381 against 376.
-bool adjoint_tiles(const int n[3]) { return (long long)n[0] * n[1] * n[2] < 400000; }
+// Grids whose adjoint is adj_small along every axis.  A rolling lane differentiates
+// every face that reaches its segment, 2R - 1 more than it owns, one after another,
+// and small grids give it few lanes.  Measured J^T w, rolls (with rows or adj_x along
+// x) -> adj_small, us:
+//   cells      33x20x17   48^3        64^3        72^3        96^3        128x128x64
+//   WENO5 FP32  82 -> 14   91 -> 39    84 -> 57   122 -> 113  148 -> 180  155 -> 179
+//   WENO5 FP64 115 -> 18  132 -> 57   132 -> 98   196 -> 179  264 -> 331  283 -> 346
+//   WENO7 FP32 139 -> 16  151 -> 46   145 -> 70   196 -> 125  247 -> 210  251 -> 236
+//   WENO7 FP64 168 -> 21  198 -> 71   186 -> 120  308 -> 214  370 -> 408  388 -> 445
+// so the line lies at 400 000 cells, and at 1.1 million for WENO7 in FP32, whose
+// rolling window costs it a wave per SIMD.
+bool adjoint_small(const int n[3], int order, int elem) {
+    return (long long)n[0] * n[1] * n[2] < (order == 7 && elem == 4 ? 1100000LL : 400000LL);
+}
 
 // Segment of the rolling adjoint: the longest of 24, 16 and 8 positions (each
 // segment differentiates 2R - 1 extra faces) that still gives two blocks per CU;
@@ -967,28 +1174,25 @@ int adjoint_segment(int nd, unsigned chunks, int elem) {
     return nd < 8 ? nd : 8;
 }
 
-template <class T, int ORDER, int DIR, int TX>
-static void launch_adjoint_tiles(const AdjArgs<T>& a, long long nlines, hipStream_t s) {
-    constexpr int TY = 256 / TX;
-    const Lin3<T> none = {(T)0, (T)0, (T)0, nullptr, nullptr, nullptr};
-    const long long ntx = (a.n[DIR] + TX - 1) / TX, nrt = (nlines + TY - 1) / TY;
-    adj_tile<T, ORDER, DIR, TX, TY><<<dim3((unsigned)(ntx * nrt)), 256, 0, s>>>(a, none);
+template <class T, int ORDER, int DIR>
+static void launch_adjoint_small(const AdjArgs<T>& a, const Lin3<T>& init, hipStream_t s) {
+    const long long lines = (long long)a.n[0] * a.n[1] * a.n[2] / a.n[DIR];
+    const long long ntx = (a.n[DIR] + kSmallTX - 1) / kSmallTX, nrt = (lines + kSmallTY - 1) / kSmallTY;
+    adj_small<T, ORDER, DIR><<<dim3((unsigned)(ntx * nrt)), kSmallLanes, 0, s>>>(a, init);
 }
 
 template <class T>
 hipError_t launch_adjoint_sweep(int dir, int order, AdjArgs<T> a, hipStream_t s) {
-    if ((dir != 1 && dir != 2) || !a.pk) return hipErrorInvalidValue;
-    const int nd = a.n[dir];
-    const long long plane = dir == 1 ? (long long)a.n[0] * a.n[2] : (long long)a.n[0] * a.n[1];
-    if (adjoint_tiles(a.n)) {
-        // WENO7 tiles are 32 x 8: the LDS of a 16 x 16 tile (95 KB in FP64) keeps a
-        // second block off the CU (64^3 FP64: 124 against 167 us per J^T w; WENO5 FP32 75 against 62)
-        if (order == 5 && dir == 1) launch_adjoint_tiles<T, 5, 1, 16>(a, plane, s);
-        else if (order == 5) launch_adjoint_tiles<T, 5, 2, 16>(a, plane, s);
-        else if (dir == 1) launch_adjoint_tiles<T, 7, 1, 32>(a, plane, s);
-        else launch_adjoint_tiles<T, 7, 2, 32>(a, plane, s);
+    if (dir != 1 && dir != 2) return hipErrorInvalidValue;
+    if (adjoint_small(a.n, order, (int)sizeof(T))) {
+        const Lin3<T> none = {(T)0, (T)0, (T)0, nullptr, nullptr, nullptr};
+        if (order == 5) dir == 1 ? launch_adjoint_small<T, 5, 1>(a, none, s) : launch_adjoint_small<T, 5, 2>(a, none, s);
+        else dir == 1 ? launch_adjoint_small<T, 7, 1>(a, none, s) : launch_adjoint_small<T, 7, 2>(a, none, s);
         return hipGetLastError();
     }
+    if (!a.pk) return hipErrorInvalidValue;
+    const int nd = a.n[dir];
+    const long long plane = dir == 1 ? (long long)a.n[0] * a.n[2] : (long long)a.n[0] * a.n[1];
     const unsigned gx = (unsigned)((plane + 255) / 256);
     a.seg = adjoint_segment(nd, gx, (int)sizeof(T));
     const unsigned gy = (nd + a.seg - 1) / a.seg;
@@ -1043,20 +1247,25 @@ hipError_t launch_adjoint_x(int order, AdjArgs<T> a, Lin3<T> init, hipStream_t s
         else launch_adjoint_rows<T, 7>(a, init, s);
         return hipGetLastError();
     }
-    const int tx = adjoint_tile_x(a.n[0]);
-    const int ty = tx == 64 ? 4 : 256 / tx;
-    const long long ntx = (a.n[0] + tx - 1) / tx;
-    const long long nrt = ((long long)a.n[1] * a.n[2] + ty - 1) / ty;
-    const dim3 grid((unsigned)(ntx * nrt));
-    if (order == 5) {
-        if (tx == 64) adj_tile<T, 5, 0, 64, 4><<<grid, 256, 0, s>>>(a, init);
-        else if (tx == 32) adj_tile<T, 5, 0, 32, 8><<<grid, 256, 0, s>>>(a, init);
-        else adj_tile<T, 5, 0, 16, 16><<<grid, 256, 0, s>>>(a, init);
-    } else {
-        if (tx == 64) adj_tile<T, 7, 0, 64, 4><<<grid, 256, 0, s>>>(a, init);
-        else if (tx == 32) adj_tile<T, 7, 0, 32, 8><<<grid, 256, 0, s>>>(a, init);
-        else adj_tile<T, 7, 0, 16, 16><<<grid, 256, 0, s>>>(a, init);
+    // adj_small on whatever size: three barriers a tile where adj_x has eleven.  Only
+    // FP32 WENO5, whose faces are the cheapest, is ahead with adj_x's longer tiles on
+    // large grids.  J^T w, adj_x -> adj_small along x, us: 130x128x128 FP64 915 -> 868,
+    // WENO7 1253 -> 1171, FP32 WENO7 614 -> 578, but FP32 WENO5 390 -> 393; 300x200x60
+    // FP64 1326 -> 1319, WENO7 1680 -> 1632, FP32 WENO7 846 -> 784, FP32 WENO5 545 -> 570.
+    if constexpr (sizeof(T) == 4) {
+        if (order == 5 && !adjoint_small(a.n, order, (int)sizeof(T))) {
+            const int tx = adjoint_tile_x(a.n[0]);
+            const int ty = tx == 64 ? 4 : 256 / tx;
+            const long long ntx = (a.n[0] + tx - 1) / tx;
+            const long long nrt = ((long long)a.n[1] * a.n[2] + ty - 1) / ty;
+            const dim3 grid((unsigned)(ntx * nrt));
+            if (tx == 64) adj_x<T, 64, 4><<<grid, 256, 0, s>>>(a, init);
+            else if (tx == 32) adj_x<T, 32, 8><<<grid, 256, 0, s>>>(a, init);
+            else adj_x<T, 16, 16><<<grid, 256, 0, s>>>(a, init);
+            return hipGetLastError();
+        }
     }
+    order == 5 ? launch_adjoint_small<T, 5, 0>(a, init, s) : launch_adjoint_small<T, 7, 0>(a, init, s);
     return hipGetLastError();
 }
 

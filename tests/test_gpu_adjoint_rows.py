@@ -182,3 +182,28 @@ def test_yz_adjoint_tiles_and_rolls_match_reference(case, order):
     ref = torch.autograd.grad(L, ut, torch.tensor(w, device="cuda"))[0].cpu().numpy()
     err = np.abs(got - ref).reshape(5, -1).max(axis=1) / max(np.abs(ref).max(), np.abs(w).max() / min(spec["h"]))
     assert np.all(err <= 1e-12), err
+
+
+@pytest.mark.parametrize("order", [5, 7])
+@pytest.mark.parametrize("prec", ["RH_PREC_FP64", "RH_PREC_FP32"])
+@pytest.mark.parametrize("bc", [P, O])
+def test_long_x_adjoint_repeats_the_short_one(bc, prec, order):
+    """A line of 401 000 cells that repeats one of 802: the x adjoint of large
+    grids gives the bits of the small grids' at every cell whose stencils see the
+    same data (all of them when periodic; up to 401 cells from either outflow end)."""
+    rh = rh_module()
+    spec = inputs.random_smooth((401, 1, 1), h=0.1, seed=306, order=order, bc=(bc, P, P))
+    w1 = np.random.default_rng(10).normal(size=(5, 1, 1, 401))
+
+    def vjp(copies):
+        s = dict(spec, shape=(401 * copies, 1, 1), prim=np.concatenate([spec["prim"]] * copies, axis=-1))
+        h = rh.Hydro.from_spec(s, precision=getattr(rh, prec))
+        got = h.vjp(oracle.prim2con(s["prim"]), np.concatenate([w1] * copies, axis=-1), t=0.1).cpu().numpy()
+        h.close()
+        return got.reshape(5, -1)
+
+    short, long = vjp(2), vjp(1000)
+    assert np.array_equal(long[:, :401], short[:, :401])
+    assert np.array_equal(long[:, -401:], short[:, -401:])
+    if bc == P:
+        assert np.array_equal(long, np.concatenate([short] * 500, axis=1))
