@@ -1161,17 +1161,39 @@ bool adjoint_small(const int n[3], int order, int elem) {
     return (long long)n[0] * n[1] * n[2] < (order == 7 && elem == 4 ? 1100000LL : 400000LL);
 }
 
-// Segment of the rolling adjoint: the longest of 24, 16 and 8 positions (each
-// segment differentiates 2R - 1 extra faces) that still gives two blocks per CU;
-// FP64 blocks fill their CU, so one block on most CUs is enough there.  96^3 FP32 WENO5
-// 159 us at 16, 138 at 8; FP64 WENO7 376 at 16, 407 at 8; 256^3 FP32 WENO5 1700 at 32,
-// 1608 at 24, FP64 4235 and 4041.
-int adjoint_segment(int nd, unsigned chunks, int elem) {
-    for (int seg : {24, 16, 8}) {
+// Segment of the rolling adjoint: the length with the least estimated time, in
+// units of one face of a block that has its CU to itself.  A lane differentiates
+// seg + 2R - 1 faces after a fill worth about four; occ blocks share a CU (waves per
+// SIMD that the registers allow) and slow each other to occ q.  Every length is
+// tried, because whether the last blocks leave the chip idle counts for more than
+// a few extra faces; a quarter of the estimate assumes that no CU is ever idle, as
+// blocks of many rounds drift apart.  Lengths past 24 (WENO7 32) measured no faster.
+// Against all lengths measured on nine grids of 405 000 to 16.8 million cells, the choices
+// are within 7% of the best, 2% on average (the longest of 24, 16 and 8 with two
+// blocks per CU: 28% and 6%).  J^T w by that rule and by this one, us: 96^3 FP64 WENO5 263
+// -> 252, WENO7 353 -> 340; 110^3 FP64 WENO7 716 -> 567, FP32 WENO5 251 -> 238; 160^3 FP64
+// WENO5 1416 -> 1308, WENO7 1781 -> 1667; 256^3 FP64 WENO7 5433 -> 5250; the largest loss
+// 203x150x97 FP64 WENO5 1008 -> 1054.
+int adjoint_segment(int nd, unsigned chunks, int order, int elem) {
+    const int occ = elem == 4 ? 3 : order == 5 ? 2 : 1;
+    const double q = occ == 3 ? 0.6 : occ == 2 ? 0.8 : 1.0;
+    const int cap = order == 5 ? 24 : 32;
+    int best = nd;
+    double best_t = 1e300;
+    for (int seg = nd < 4 ? nd : 4; seg <= (nd < cap ? nd : cap); ++seg) {
         const long long blocks = (long long)chunks * ((nd + seg - 1) / seg);
-        if (blocks >= (elem == 8 && seg == 16 ? 200 : 512)) return seg < nd ? seg : nd;
+        const double alone = 4.0 + seg + order, all = occ * q * alone;   // 2R - 1 = order faces past the segment
+        const long long per_cu = (blocks + 255) / 256, rest = per_cu % occ;
+        double t = (per_cu / occ) * all;
+        if (rest) t += occ > 1 ? alone * (1.0 + (occ * q - 1.0) * (rest - 1) / (occ - 1)) : alone;
+        const double busy = blocks * q * alone / 256.0;
+        t = 0.75 * t + 0.25 * (busy > alone ? busy : alone);
+        if (t < best_t * (1.0 - 1e-9)) {
+            best_t = t;
+            best = seg;
+        }
     }
-    return nd < 8 ? nd : 8;
+    return best;
 }
 
 template <class T, int ORDER, int DIR>
@@ -1194,7 +1216,7 @@ hipError_t launch_adjoint_sweep(int dir, int order, AdjArgs<T> a, hipStream_t s)
     const int nd = a.n[dir];
     const long long plane = dir == 1 ? (long long)a.n[0] * a.n[2] : (long long)a.n[0] * a.n[1];
     const unsigned gx = (unsigned)((plane + 255) / 256);
-    a.seg = adjoint_segment(nd, gx, (int)sizeof(T));
+    a.seg = adjoint_segment(nd, gx, order, (int)sizeof(T));
     const unsigned gy = (nd + a.seg - 1) / a.seg;
     const dim3 grid(gx, gy), block(256);
     const bool hub = a.bc == RH_BC_HUBBLE;
