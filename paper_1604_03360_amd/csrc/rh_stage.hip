@@ -196,13 +196,13 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
             unsigned dummy = 0;   // floors are counted when the cell's own plane is staged
             if constexpr (LOCAL) {
                 double kap, Mxs, Mys, Mzs, p;
-                recover_kp3((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, Mzs, p, dummy);
+                recover_kp3<HUB>((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, Mzs, p, dummy);
                 VZ = (T)(kap * Mzs);
                 P = (T)p;
                 speed = (T)max_char_speed(kap * Mzs, kap * kap * (Mxs * Mxs + Mys * Mys + Mzs * Mzs), 1.0 / 3.0);
             } else {
                 double vd, p;
-                recover_vp<2>((double)u[0], (double)u[1], (double)u[2], (double)u[3], vd, p, dummy);
+                recover_vp<2, HUB>((double)u[0], (double)u[1], (double)u[2], (double)u[3], vd, p, dummy);
                 VZ = (T)vd;
                 P = (T)p;
             }
@@ -234,10 +234,10 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
             } else {
                 double kap, Mxs, Mys, p;
                 if constexpr (!LOCAL) {
-                    recover_kp((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, p, c0);
+                    recover_kp<HUB>((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, p, c0);
                 } else {
                     double Mzs;
-                    recover_kp3((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, Mzs, p, c0);
+                    recover_kp3<HUB>((double)u[0], (double)u[1], (double)u[2], (double)u[3], kap, Mxs, Mys, Mzs, p, c0);
                     v2 = kap * kap * (Mxs * Mxs + Mys * Mys + Mzs * Mzs);
                     cs2 = 1.0 / 3.0;
                 }
@@ -286,10 +286,10 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
                 double hk, hMx, hMy, hp;
                 unsigned hcl = 0;
                 if constexpr (!LOCAL) {
-                    recover_kp((double)hu[0], (double)hu[1], (double)hu[2], (double)hu[3], hk, hMx, hMy, hp, hcl);
+                    recover_kp<HUB>((double)hu[0], (double)hu[1], (double)hu[2], (double)hu[3], hk, hMx, hMy, hp, hcl);
                 } else {
                     double hMz;
-                    recover_kp3((double)hu[0], (double)hu[1], (double)hu[2], (double)hu[3], hk, hMx, hMy, hMz, hp,
+                    recover_kp3<HUB>((double)hu[0], (double)hu[1], (double)hu[2], (double)hu[3], hk, hMx, hMy, hMz, hp,
                                 hcl);
                     hv2 = hk * hk * (hMx * hMx + hMy * hMy + hMz * hMz);
                     hcs2 = 1.0 / 3.0;

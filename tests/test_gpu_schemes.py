@@ -395,3 +395,31 @@ def test_scheme_errors():
     with pytest.raises(rh.RHError) as ei:
         rh.Hydro.from_spec(spec)
     assert ei.value.status == rh.RH_E_NOTSUP
+
+
+@pytest.mark.parametrize("prec", ["RH_PREC_FP64", "RH_PREC_FP32"])
+@pytest.mark.parametrize("side", [1, -1])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_musta_minmod_takes_a_nan_difference_for_zero(axis, side, prec):
+    """A cell of NaN two cells away only zeroes the slope between (bitwise as where
+    that difference has the opposite sign), and the cells beyond do not see it."""
+    import torch
+    rh = rh_module()
+    spec = inputs.random_smooth((9, 10, 11), h=0.1, seed=401, order=2)
+    u = oracle.prim2con(spec["prim"]).reshape(5, 11, 10, 9)
+
+    def rhs(state):
+        h = rh.Hydro.from_spec(spec, precision=getattr(rh, prec))
+        h.state.copy_(torch.tensor(state).reshape(h.state.shape).to(h.state.dtype))
+        L = h.apply_L().double().cpu().numpy().reshape(5, 11, 10, 9)
+        h.close()
+        return L
+
+    at = lambda d: (slice(None),) + tuple(5 + side * d * (k == 2 - axis) for k in range(3))
+    bad, turned = u.copy(), u.copy()
+    bad[at(0)] = np.nan
+    turned[at(0)] = u[at(2)]
+    L0, Lbad, Lturned = rhs(u), rhs(bad), rhs(turned)
+    assert np.isnan(Lbad[at(0)]).all()
+    assert np.array_equal(Lbad[at(2)], Lturned[at(2)])
+    assert np.array_equal(Lbad[at(3)], L0[at(3)])
