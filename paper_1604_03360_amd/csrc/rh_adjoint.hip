@@ -679,7 +679,8 @@ __global__ void __launch_bounds__(256) adj_x(AdjArgs<T> A, Lin3<T> init) {
 // along the axis x 4 lines and differentiates the faces of all five components
 // at once, one (component, face) per lane; the partials go to LDS, are gathered
 // one (component, cell) per lane, and the lane that owns the cell applies the
-// flux Jacobian: three barriers in all (a component at a time as in adj_x: eleven).
+// flux Jacobian: three barriers in all, five with HALF (a component at a time as in adj_x:
+// eleven).
 // Each block recovers the primitives of the cells it stages (FP64, as adj_pack):
 // reading them from a pack measured no faster (130x128x128 FP64 868 us against
 // 877) and costs small grids a launch.  J^T w at 33x20x17 FP64 WENO7: 168 us with
@@ -737,8 +738,22 @@ __device__ __forceinline__ void line_state(const AdjArgs<T>& A, int m, int line,
 
 constexpr int kSmallTX = 16, kSmallTY = 4, kSmallLanes = 512;
 
-template <class T, int ORDER, int DIR>
-__global__ void __launch_bounds__(kSmallLanes) adj_small(AdjArgs<T> A, Lin3<T> init) {
+// Three blocks a CU in FP64 (six waves per SIMD): what the owners hold from the
+// recovery to the end (WENO7: their state as well) is parked in LDS, which saves
+// the registers, and WENO7 with HALF takes the plus and the minus partials
+// through the same LDS one after the other, two barriers more.  J^T w at two
+// blocks a CU and at three, FP64, us: 64^3 WENO5 101 -> 91, WENO7 124 -> 116; 72^3 181 -> 155
+// and 223 -> 198; but WENO7 at 33x20x17, where every block has its place at
+// once, 20.1 -> 21.0, so HALF begins where two blocks a CU are not enough.
+template <class T, int ORDER, bool HALF>
+struct AdjSmall {
+    static constexpr bool three = sizeof(T) == 8 && (ORDER == 5 || HALF);
+    static constexpr int waves = sizeof(T) == 4 ? 8 : three ? 6 : 4;
+    static constexpr int park = !three ? 0 : ORDER == 5 ? 5 : 10;
+};
+
+template <class T, int ORDER, int DIR, bool HALF>
+__global__ void __launch_bounds__(kSmallLanes, (AdjSmall<T, ORDER, HALF>::waves)) adj_small(AdjArgs<T> A, Lin3<T> init) {
     constexpr int R = (ORDER + 1) / 2, K = 2 * R - 1;
     constexpr int TX = kSmallTX, TY = kSmallTY, CELLS = TX * TY;
     constexpr int NF = TX + 2 * R - 1;   // faces x0-R .. x0+TX+R-2 (face i: between cells i and i+1)
@@ -749,8 +764,11 @@ __global__ void __launch_bounds__(kSmallLanes) adj_small(AdjArgs<T> A, Lin3<T> i
     static_assert(5 * NF * TY <= kSmallLanes, "one face and component per lane");
     __shared__ T sfp[5][NC * TY], sfm[5][NC * TY];   // split fluxes, [position][line]
     __shared__ T sw[5][NW * TY];                     // weights
-    __shared__ T sp[5][K][NF * TY], sm[5][K][NF * TY];   // partials of face f for cells f + k (minus: f + 1 + k)
+    __shared__ T spm[HALF ? 1 : 2][5][K][NF * TY];   // partials of face f for cells f + k (minus: f + 1 + k)
+    T (*sp)[K][NF * TY] = spm[0], (*sm)[K][NF * TY] = spm[HALF ? 0 : 1];
     __shared__ T sa[10][CELLS];                      // split-flux adjoints of the tile's cells
+    constexpr int PARK = AdjSmall<T, ORDER, HALF>::park;
+    __shared__ T sr[PARK ? PARK : 1][PARK ? CELLS : 1];   // what their owners keep until the end
     const int nd = A.n[DIR];
     const int nlines = DIR == 0 ? A.n[1] * A.n[2] : DIR == 1 ? A.n[0] * A.n[2] : A.n[0] * A.n[1];
     const int ntx = (nd + TX - 1) / TX;
@@ -819,13 +837,24 @@ __global__ void __launch_bounds__(kSmallLanes) adj_small(AdjArgs<T> A, Lin3<T> i
         kM2 = (T)o.kap_M2;
         pE = (T)o.p_E;
         pM2 = (T)o.p_M2;
+        if constexpr (PARK >= 5) {
+            sr[0][own] = kap;
+            sr[1][own] = kE;
+            sr[2][own] = kM2;
+            sr[3][own] = pE;
+            sr[4][own] = pM2;
+        }
+        if constexpr (PARK >= 10) {
+#pragma unroll
+            for (int f = 0; f < 5; ++f) sr[5 + f][own] = uf[f];
+        }
     }
     __syncthreads();
 
+    const int fc = tid / (NF * TY), fj = tid - fc * (NF * TY);
+    T op[K], om[K];
     if (tid < 5 * NF * TY) {
-        const int c = tid / (NF * TY), j = tid - c * (NF * TY), fl = j / TY;
-        const int i = x0 - R + fl;
-        T op[K], om[K];
+        const int c = fc, j = fj, i = x0 - R + j / TY;
 #pragma unroll
         for (int k = 0; k < K; ++k) op[k] = om[k] = (T)0;
         if ((periodic || (i >= -1 && i <= nd - 1)) && r0 + (j & (TY - 1)) < nlines) {
@@ -854,39 +883,54 @@ __global__ void __launch_bounds__(kSmallLanes) adj_small(AdjArgs<T> A, Lin3<T> i
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            sp[c][k][j] = op[k];
-            sm[c][k][j] = om[k];
+            sp[fc][k][fj] = op[k];
+            if constexpr (!HALF) sm[fc][k][fj] = om[k];
         }
     }
     __syncthreads();
     // partials reaching staged cell q: plus from faces q-k, minus from faces q-1-k
-    if (tid < 5 * CELLS) {
-        const int c = tid / CELLS, cell = tid - c * CELLS, lx = cell / TY, ly = cell & (TY - 1);
-        const int q = lx + 2 * R - 1;   // every face reaching an owned cell is in the tile
-        T a_p = (T)0, a_m = (T)0;
+    const int gc = tid / CELLS, cell = tid - gc * CELLS, gly = cell & (TY - 1);
+    const int q = cell / TY + 2 * R - 1;   // every face reaching an owned cell is in the tile
+    const int gx = x0 + cell / TY;
+    const bool fold = A.bc == RH_BC_OUTFLOW && (gx == 0 || gx == nd - 1);
+    auto gather = [&](const T (*part)[NF * TY], int f0) {
+        T a = (T)0;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            a_p += sp[c][k][(q - k) * TY + ly];
-            a_m += sm[c][k][(q - 1 - k) * TY + ly];
-        }
-        const int gx = x0 + lx;
-        if (A.bc == RH_BC_OUTFLOW && (gx == 0 || gx == nd - 1)) {
+        for (int k = 0; k < K; ++k) a += part[k][(q - f0 - k) * TY + gly];
+        if (fold) {
             // ghost positions beyond the edge fold onto the edge cell (same state, so
             // their split-flux adjoints add before the Jacobian)
             for (int e = 1; e < 2 * R; ++e) {
-                const int qe = gx == 0 ? q - e : q + e;
-                for (int k = 0; k < K; ++k) {
-                    const int fp_ = qe - k, fm_ = qe - 1 - k;
-                    if (fp_ >= 0 && fp_ < NF) a_p += sp[c][k][fp_ * TY + ly];
-                    if (fm_ >= 0 && fm_ < NF) a_m += sm[c][k][fm_ * TY + ly];
-                }
+                const int qe = (gx == 0 ? q - e : q + e) - f0;
+                for (int k = 0; k < K; ++k)
+                    if (qe - k >= 0 && qe - k < NF) a += part[k][(qe - k) * TY + gly];
             }
         }
-        sa[c][cell] = a_p;
-        sa[5 + c][cell] = a_m;
+        return a;
+    };
+    if (tid < 5 * CELLS) sa[gc][cell] = gather(sp[gc], 0);
+    if constexpr (HALF) {
+        __syncthreads();
+        if (tid < 5 * NF * TY) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) sm[fc][k][fj] = om[k];
+        }
+        __syncthreads();
     }
+    if (tid < 5 * CELLS) sa[5 + gc][cell] = gather(sm[gc], 1);
     __syncthreads();
     if (!owner) return;
+    if constexpr (PARK >= 5) {
+        kap = sr[0][own];
+        kE = sr[1][own];
+        kM2 = sr[2][own];
+        pE = sr[3][own];
+        pM2 = sr[4][own];
+    }
+    if constexpr (PARK >= 10) {
+#pragma unroll
+        for (int f = 0; f < 5; ++f) uf[f] = sr[5 + f][own];
+    }
     T lam[5], g[5];
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
@@ -1152,9 +1196,9 @@ static unsigned blocks_for(long long n) {
 // x) -> adj_small, us:
 //   cells      33x20x17   48^3        64^3        72^3        96^3        128x128x64
 //   WENO5 FP32  82 -> 14   91 -> 39    84 -> 57   122 -> 113  148 -> 180  155 -> 179
-//   WENO5 FP64 115 -> 18  132 -> 57   132 -> 98   196 -> 179  264 -> 331  283 -> 346
+//   WENO5 FP64 115 -> 18  132 -> 56   132 -> 91   196 -> 155  264 -> 331  283 -> 346
 //   WENO7 FP32 139 -> 16  151 -> 46   145 -> 70   196 -> 125  247 -> 210  251 -> 236
-//   WENO7 FP64 168 -> 21  198 -> 71   186 -> 120  308 -> 214  370 -> 408  388 -> 445
+//   WENO7 FP64 168 -> 20  198 -> 69   186 -> 117  308 -> 200  370 -> 408  388 -> 445
 // so the line lies at 400 000 cells, and at 1.1 million for WENO7 in FP32, whose
 // rolling window costs it a wave per SIMD.
 bool adjoint_small(const int n[3], int order, int elem) {
@@ -1200,7 +1244,14 @@ template <class T, int ORDER, int DIR>
 static void launch_adjoint_small(const AdjArgs<T>& a, const Lin3<T>& init, hipStream_t s) {
     const long long lines = (long long)a.n[0] * a.n[1] * a.n[2] / a.n[DIR];
     const long long ntx = (a.n[DIR] + kSmallTX - 1) / kSmallTX, nrt = (lines + kSmallTY - 1) / kSmallTY;
-    adj_small<T, ORDER, DIR><<<dim3((unsigned)(ntx * nrt)), kSmallLanes, 0, s>>>(a, init);
+    const dim3 grid((unsigned)(ntx * nrt));
+    if constexpr (sizeof(T) == 8 && ORDER == 7) {
+        if (ntx * nrt > 512) {
+            adj_small<T, ORDER, DIR, true><<<grid, kSmallLanes, 0, s>>>(a, init);
+            return;
+        }
+    }
+    adj_small<T, ORDER, DIR, false><<<grid, kSmallLanes, 0, s>>>(a, init);
 }
 
 template <class T>
