@@ -1194,15 +1194,17 @@ static unsigned blocks_for(long long n) {
 // every face that reaches its segment, 2R - 1 more than it owns, one after another,
 // and small grids give it few lanes.  Measured J^T w, rolls (with rows or adj_x along
 // x) -> adj_small, us:
-//   cells      33x20x17   48^3        64^3        72^3        96^3        128x128x64
-//   WENO5 FP32  82 -> 14   91 -> 39    84 -> 57   122 -> 113  148 -> 180  155 -> 179
-//   WENO5 FP64 115 -> 18  132 -> 56   132 -> 91   196 -> 155  264 -> 331  283 -> 346
-//   WENO7 FP32 139 -> 16  151 -> 46   145 -> 70   196 -> 125  247 -> 210  251 -> 236
-//   WENO7 FP64 168 -> 20  198 -> 69   186 -> 117  308 -> 200  370 -> 408  388 -> 445
-// so the line lies at 400 000 cells, and at 1.1 million for WENO7 in FP32, whose
-// rolling window costs it a wave per SIMD.
+//   cells      33x20x17   48^3        64^3        72^3        80^3        96^3
+//   WENO5 FP32  82 -> 14   91 -> 39    84 -> 57   122 -> 113              148 -> 180
+//   WENO5 FP64 115 -> 18  132 -> 56   132 -> 91   196 -> 155  198 -> 183  251 -> 276
+//   WENO7 FP32 139 -> 16  151 -> 46   145 -> 70   196 -> 125              247 -> 210
+//   WENO7 FP64 168 -> 20  198 -> 69   186 -> 117  308 -> 200  271 -> 231  343 -> 352
+// so the line lies at 400 000 cells in FP32 and 600 000 in FP64 (88^3: 249 -> 255 and
+// 336 -> 322), and at 1.1 million for WENO7 in FP32, whose rolling window costs it a
+// wave per SIMD (128x128x64: 251 -> 236).
 bool adjoint_small(const int n[3], int order, int elem) {
-    return (long long)n[0] * n[1] * n[2] < (order == 7 && elem == 4 ? 1100000LL : 400000LL);
+    const long long cells = (long long)n[0] * n[1] * n[2];
+    return cells < (elem == 8 ? 600000 : order == 7 ? 1100000 : 400000);
 }
 
 // Segment of the rolling adjoint: the length with the least estimated time, in

@@ -139,10 +139,13 @@ def test_row_vjp_is_bitwise_the_tiled_kernel(tmp_path):
 
 
 LARGE = {
-    # above the size from which y and z roll instead of taking tiles; ragged axes
+    # around and above the sizes from which y and z roll instead of taking tiles; ragged axes
     "periodic": lambda o: inputs.random_smooth((76, 75, 71), h=0.1, seed=301, order=o),
     "outflow": lambda o: inputs.random_smooth((61, 83, 81), h=0.1, seed=302, order=o, bc=(inputs.BC_OUTFLOW,) * 3),
     "hubble": lambda o: inputs.hubble(n=75, order=o, half_width=3.0),
+    "periodic_600k": lambda o: inputs.random_smooth((86, 85, 83), h=0.1, seed=307, order=o),
+    "outflow_600k": lambda o: inputs.random_smooth((71, 93, 92), h=0.1, seed=308, order=o, bc=(inputs.BC_OUTFLOW,) * 3),
+    "hubble_600k": lambda o: inputs.hubble(n=85, order=o, half_width=3.0),
 }
 # below it: one short of, at and past a tile edge along every axis
 SMALL = {
