@@ -81,10 +81,11 @@ typedef int rh_status;
  * global splitting and the conformal fluid both give bitwise the same results;
  * MUSTA-FORCE, local splitting and the ideal gas exist on RH_PATH_STAGE only.
  * RH_PATH_AUTO (the default) takes RH_PATH_STAGE for batches and where only it
- * applies, and for other single grids the faster of the two: RH_PATH_STAGE for
- * three-dimensional grids below a size that depends on scheme, precision and
- * boundaries, RH_PATH_SWEEPS otherwise and while per-launch timing is on
- * (rh_set_timing), so that the times are those of the directional sweeps.  On
+ * applies, and for other three-dimensional grids the path whose estimated step is
+ * shorter (from scheme, precision and shape; axes of a few cells along x or y keep
+ * the sweeps).  One- and two-dimensional grids take RH_PATH_SWEEPS, and so does every
+ * grid that can while per-launch timing is on (rh_set_timing): the times are then
+ * those of the directional sweeps, not of an untimed run.  On
  * RH_PATH_AUTO rh_step advances one-dimensional grids of up to 8192 cells
  * (periodic or outflow, any scheme) several steps per launch, without graphs. */
 #define RH_PATH_AUTO   0

@@ -100,6 +100,8 @@ struct rh_plan {
     int path = RH_PATH_AUTO;
     int stage_tx = 16;
     int stage_seg = 0;           // 0: default segment for the grid
+    int default_seg = 1;         // that default, for stage_tx
+    bool auto_stage = false;     // RH_PATH_AUTO takes the fused stage
     // one captured step, replayed by rh_step when enabled
     bool graph_on = false;
     hipStream_t cap_stream = nullptr;
@@ -232,41 +234,68 @@ hipError_t launch_stage_of(const rh_grid_desc& d, int tx, bool hub, const rh::St
 bool needs_recovery(const rh_grid_desc& d) { return d.eos == RH_EOS_IDEAL && d.scheme != RH_SCHEME_MUSTA; }
 
 // Grids whose evaluations RH_PATH_AUTO gives to the fused stage (bitwise the
-// results of the sweeps).  One launch per stage instead of three, with as many
-// blocks as the chip takes, wins wherever latency or the L accumulator's traffic
-// counts: 31 against 135 us per FP32 WENO5 step at 33 x 20 x 17, 60 against 232 at
-// 64^3, 425 against 500 at 203 x 150 x 97, 275 against 294 at 128^3, 1970 against
-// 2260 at 256^3 with outflow boundaries.  The sweeps are kept
-//   - for WENO5 where the fused x-y sweep takes large grids in full rows (256^3
-//     periodic: 1870 against 1970 us FP32, 3520 against 3500 FP64; rows of 192 leave
-//     it behind, 865 against 844),
-//   - for WENO7 from the size where the stage's fewer waves (two per SIMD in FP32,
-//     one in FP64) cost more than its traffic saves (FP32: 244 against 350 us at
-//     96^3, 519 against 509 at 128^3; FP64: 354 against 370 at 96^3, 781 against 690
-//     at 128^3, 6290 against 4760 at 256^3).
+// results of the sweeps): those of which the estimated step is shorter that way.
+// One launch per stage instead of three wins wherever latency or the L accumulator's
+// traffic counts, unless its tiles stay empty: a tile is 16 x 16, so an axis of a few
+// cells along x or y leaves most of its lanes idle, where the sweeps only pad x.
+// The stage's estimate is linear in the planes of its segment model.  The sweeps' joins
+// a latency and a throughput (us per cell, less where the fused x-y sweep takes rows of
+// 256, and per cell that pads x to 16) as the 1.5-norm.  Fitted to both paths timed at 170
+// random and 70 chosen shapes of 2 .. 4096 cells an axis, weighted to where they are close:
+// the choice costs 0.1 - 0.3% on average against the faster path, and more than 3% at
+// one shape in 30.
+// Sweeps and stage, us per step:
+//                  FP32 WENO5    FP64 WENO5    FP32 WENO7    FP64 WENO7
+//   33x20x17        135    31
+//   64^3            228    56     235    76     292    89     297   114
+//   128^3           293   265     508   435     499   513     680   766
+//   192^3           852   833    1829  1519    1509  1691    2337  2748
+//   256^3          1851  1966    3463  3442    3028  3845    4661  6212
+//   256x256x32      296   265     448   437     481   515     611   765
+//   512x2x512       188   393     233   678     270   846     293  1389
+//   2x512x512       398   479     478   801     557   975     621  1481
+//   300x3x300       169   160     195   268     232   333     246   531
+//   1024x4x1024     628  1458    1204  2608     971  3275    1539  5533
+//   256x8x256       192   140     204   216     276   261     267   373
+//   1024x1024x4     609   499    1169   916     974  1012    1505  1743
+struct PathCost {
+    double stage, plane;                    // stage: us fixed, and per plane of the segment model
+    double sweeps, cell, row_cell, x_pad;   // sweeps: us of latency, per 10^6 cells, the same in rows of 256, per 10^6 padding cells
+};
+constexpr PathCost kPathCost[2][2] = {   // [WENO5, WENO7][FP32, FP64]
+    {{5.6, 15.5, 165.0, 128.0, 98.0, 78.0}, {1.9, 17.2, 160.0, 255.0, 208.0, 102.0}},
+    {{9.5, 23.8, 229.0, 210.0, 198.0, 125.0}, {0.0, 22.4, 199.0, 305.0, 285.0, 169.0}},
+};
+
 bool auto_stage(const rh_grid_desc& d) {
-    if (d.nx < 2 || d.ny < 2 || d.nz < 2) return false;
-    const long long cells = (long long)d.nx * d.ny * d.nz;
-    const bool fp32 = d.precision == RH_PREC_FP32;
-    if (d.scheme == 7) return cells < (fp32 ? 2000000 : 1200000);
+    if (d.nx < 2 || d.ny < 2 || d.nz < 2 || needs_stage(d)) return false;
     const int n[3] = {d.nx, d.ny, d.nz};
-    const bool rows = d.nx == 256 && rh::sweep_xy_applies(5, fp32 ? 4 : 8, n, d.bc[0]);
-    return !(rows && cells >= 2000000);
+    const int elem = d.precision == RH_PREC_FP32 ? 4 : 8;
+    const PathCost& c = kPathCost[d.scheme == 7][elem == 8];
+    double planes;
+    rh::stage_segment(1, &n, 16, d.scheme, elem, false, &planes);
+    const double yz = 1e-6 * d.ny * d.nz;
+    const bool rows = d.nx == 256 && rh::sweep_xy_applies(d.scheme, elem, n, d.bc[0]);
+    const double busy = yz * ((rows ? c.row_cell : c.cell) * d.nx + c.x_pad * ((16 - d.nx % 16) % 16));
+    const double sweeps = std::pow(std::pow(c.sweeps, 1.5) + std::pow(busy, 1.5), 1.0 / 1.5);
+    return c.stage + c.plane * planes < sweeps;
 }
 
 // Path of a single grid's evaluations: the fused stage where it is requested
 // or where only it implements the scheme, else RH_PATH_AUTO's choice.
 bool use_stage(const rh_plan* p) {
     if (needs_stage(p->d) || p->path == RH_PATH_STAGE) return true;
-    return p->path == RH_PATH_AUTO && !p->timing && auto_stage(p->d);
+    return p->path == RH_PATH_AUTO && !p->timing && p->auto_stage;
+}
+
+// Default z segment of a plan's fused stage, taken again when its tile changes.
+void set_default_segment(rh_plan* p) {
+    const int n[3] = {p->d.nx, p->d.ny, p->d.nz};
+    p->default_seg = rh::stage_segment(1, &n, p->stage_tx, p->d.scheme, (int)p->elem, p->d.flux_split == RH_SPLIT_LOCAL);
 }
 
 // z segment of a plan's fused stage (set by the caller, or the default).
-int plan_stage_segment(const rh_plan* p) {
-    if (p->stage_seg > 0) return p->stage_seg;
-    const int n[3] = {p->d.nx, p->d.ny, p->d.nz};
-    return rh::stage_segment(1, &n, p->stage_tx, p->d.scheme, (int)p->elem, p->d.flux_split == RH_SPLIT_LOCAL);
-}
+int plan_stage_segment(const rh_plan* p) { return p->stage_seg > 0 ? p->stage_seg : p->default_seg; }
 
 // One evaluation of L at time t on `us`; stage == 0 stores L in `lacc`,
 // otherwise the stage combine writes `uout` from `us`, `u0` and dt.
@@ -593,6 +622,8 @@ rh_status rh_plan_create(rh_plan** out, const rh_grid_desc* d) {
     p->ghosts = musta ? 2 : (d->scheme + 1) / 2;
     p->ncell = (long long)n[0] * n[1] * n[2];
     p->elem = d->precision == RH_PREC_FP32 ? 4 : 8;
+    p->auto_stage = auto_stage(p->d);
+    set_default_segment(p);
     hipError_t e;
     if ((e = hipMalloc(&p->d_clamps, sizeof(unsigned))) != hipSuccess ||
         (e = hipMalloc(&p->d_partials, 6 * rh::kTotalsBlocks * sizeof(double))) != hipSuccess ||
@@ -725,6 +756,7 @@ rh_status rh_set_stage_tuning(rh_plan* p, int tile_x, int seg_z) {
     if (seg_z < 0) return fail(RH_E_INVAL, "seg_z must be >= 0 (0 = default)");
     p->stage_tx = tile_x;
     p->stage_seg = seg_z;
+    set_default_segment(p);
     drop_graph(p);
     return RH_OK;
 }

@@ -208,8 +208,10 @@ template <class T>
 hipError_t launch_stage(int order, int tx, bool hub, bool local, int eos, const StageArgs<T>& a,
                         long long nblocks, hipStream_t s);
 // z segment of the stage kernels for a launch over ngrid grids of n[g] cells
-// (scheme 5, 7 or RH_SCHEME_MUSTA; tiles of tx, elem bytes per value).
-int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bool local);
+// (scheme 5, 7 or RH_SCHEME_MUSTA; tiles of tx, elem bytes per value), and its
+// estimated time in planes of a block that has its CU to itself.
+int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bool local,
+                  double* planes_out = nullptr);
 
 // MUSTA-FORCE stage (the same work items, with x-y tiles of kMustaTX x
 // kMustaTY cells): one launch evaluates the MUSCL + MUSTA face fluxes of x, y

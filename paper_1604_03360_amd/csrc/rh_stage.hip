@@ -555,7 +555,7 @@ template hipError_t launch_recover_ideal<double>(const StageArgs<double>&, long 
 // for 64^3 .. 160^3, both orders and precisions, and MUSTA-FORCE for 24^3 .. 256^3, the
 // choices are within 2% of the best (MUSTA-FORCE 5%).  Before, MUSTA-FORCE took segments
 // of at least 8 planes: 24^3 172 us per FP32 step, now 36; 128^3 FP64 611, now 559.
-int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bool local) {
+int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bool local, double* planes_out) {
     const bool musta = scheme == RH_SCHEME_MUSTA, light = scheme == 5 && (elem == 4 || !local);
     const int ty = musta ? kMustaTY : 256 / tx;
     int occ;
@@ -590,6 +590,7 @@ int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bo
         }
         if (seg >= planes) break;
     }
+    if (planes_out) *planes_out = best_t;
     return best;
 }
 
