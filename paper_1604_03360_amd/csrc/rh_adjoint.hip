@@ -1190,7 +1190,7 @@ static unsigned blocks_for(long long n) {
     return (unsigned)b;
 }
 
-// Grids whose adjoint is adj_small along every axis.  A rolling lane differentiates
+// Axes whose adjoint is adj_small.  A rolling lane differentiates
 // every face that reaches its segment, 2R - 1 more than it owns, one after another,
 // and small grids give it few lanes.  Measured J^T w, rolls (with rows or adj_x along
 // x) -> adj_small, us:
@@ -1201,10 +1201,23 @@ static unsigned blocks_for(long long n) {
 //   WENO7 FP64 168 -> 20  198 -> 69   186 -> 117  308 -> 200  271 -> 231  343 -> 352
 // so the line lies at 400 000 cells in FP32 and 600 000 in FP64 (88^3: 249 -> 255 and
 // 336 -> 322), and at 1.1 million for WENO7 in FP32, whose rolling window costs it a
-// wave per SIMD (128x128x64: 251 -> 236).
-bool adjoint_small(const int n[3], int order, int elem) {
-    const long long cells = (long long)n[0] * n[1] * n[2];
+// wave per SIMD (128x128x64: 251 -> 236).  A y or z axis of fewer than 16 cells counts
+// as 16, the tile it occupies, where a rolling lane takes its few cells at once: y rolled
+// -> y in tiles (z in tiles), us in the same order: 512x2x512 118 -> 297, 194 -> 479,
+// 182 -> 375, 333 -> 643; 300x3x300 86 -> 130, 121 -> 199, 120 -> 158, 194 -> 260.
+bool adjoint_small(int dir, const int n[3], int order, int elem) {
+    const long long lines = (long long)n[0] * n[1] * n[2] / n[dir];
+    const long long cells = lines * (dir > 0 && n[dir] < kSmallTX ? kSmallTX : n[dir]);
     return cells < (elem == 8 ? 600000 : order == 7 ? 1100000 : 400000);
+}
+
+// adj_x (FP32 WENO5) and the rolls read it.
+bool adjoint_reads_pack(const int n[3], int bc_x, int order, int elem) {
+    for (int d = 0; d < 3; ++d) {
+        const bool recovers = d == 0 && (adjoint_x_rows(n, bc_x) || order != 5 || elem != 4);
+        if (n[d] > 1 && !recovers && !adjoint_small(d, n, order, elem)) return true;
+    }
+    return false;
 }
 
 // Segment of the rolling adjoint: the length with the least estimated time, in
@@ -1259,7 +1272,7 @@ static void launch_adjoint_small(const AdjArgs<T>& a, const Lin3<T>& init, hipSt
 template <class T>
 hipError_t launch_adjoint_sweep(int dir, int order, AdjArgs<T> a, hipStream_t s) {
     if (dir != 1 && dir != 2) return hipErrorInvalidValue;
-    if (adjoint_small(a.n, order, (int)sizeof(T))) {
+    if (adjoint_small(dir, a.n, order, (int)sizeof(T))) {
         const Lin3<T> none = {(T)0, (T)0, (T)0, nullptr, nullptr, nullptr};
         if (order == 5) dir == 1 ? launch_adjoint_small<T, 5, 1>(a, none, s) : launch_adjoint_small<T, 5, 2>(a, none, s);
         else dir == 1 ? launch_adjoint_small<T, 7, 1>(a, none, s) : launch_adjoint_small<T, 7, 2>(a, none, s);
@@ -1328,7 +1341,7 @@ hipError_t launch_adjoint_x(int order, AdjArgs<T> a, Lin3<T> init, hipStream_t s
     // WENO7 1253 -> 1171, FP32 WENO7 614 -> 578, but FP32 WENO5 390 -> 393; 300x200x60
     // FP64 1326 -> 1319, WENO7 1680 -> 1632, FP32 WENO7 846 -> 784, FP32 WENO5 545 -> 570.
     if constexpr (sizeof(T) == 4) {
-        if (order == 5 && !adjoint_small(a.n, order, (int)sizeof(T))) {
+        if (order == 5 && !adjoint_small(0, a.n, order, (int)sizeof(T))) {
             const int tx = adjoint_tile_x(a.n[0]);
             const int ty = tx == 64 ? 4 : 256 / tx;
             const long long ntx = (a.n[0] + tx - 1) / tx;

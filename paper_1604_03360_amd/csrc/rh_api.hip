@@ -1647,7 +1647,7 @@ rh_status vjp_impl(rh_plan* p, double t, const T* u, const T* w, T* out, rh::Lin
     // the whole-row x adjoint computes the pack of its cells and stores it
     const bool x_packs = n[0] > 1 && rh::adjoint_x_rows(n, p->d.bc[0]);
     rh_status st = RH_OK;
-    if (!x_packs && !rh::adjoint_small(n, p->d.scheme, (int)sizeof(T))) {
+    if (!x_packs && rh::adjoint_reads_pack(n, p->d.bc[0], p->d.scheme, (int)sizeof(T))) {
         st = timed_launch(p, RH_KERNEL_OTHER,
                           [&] { return rh::launch_adjoint_pack<T>(u, pk, p->ncell, p->stream); }, "pack launch");
         if (st != RH_OK) return st;

@@ -76,7 +76,7 @@ struct AdjArgs {
 };
 
 // y (dir 1) or z (dir 2) axis of the adjoint: a.ub += a.scale J_dir^T w.
-// a.pk (required unless adjoint_small()) holds the recovery and its derivatives for every cell.
+// a.pk (required unless adjoint_small(dir)) holds the recovery and its derivatives for every cell.
 template <class T>
 hipError_t launch_adjoint_sweep(int dir, int order, AdjArgs<T> a, hipStream_t s);
 // Fill the six-field recovery pack of state u (layout [5][ncell] -> [6][ncell]).
@@ -92,15 +92,17 @@ struct Lin3 {
 };
 // x axis of the adjoint (LDS tiles or whole rows): a.ub = init + a.scale J_x^T w,
 // written without reading a.ub.  a.pk (required) receives the recovery pack where
-// adjoint_x_rows() holds (whole-row kernel) and elsewhere has to hold it unless
-// adjoint_small() holds.
+// adjoint_x_rows() holds (whole-row kernel) and elsewhere has to hold it where
+// adjoint_reads_pack() holds.
 template <class T>
 hipError_t launch_adjoint_x(int order, AdjArgs<T> a, Lin3<T> init, hipStream_t s);
 // True where the x adjoint takes whole periodic rows and writes the pack itself.
 bool adjoint_x_rows(const int n[3], int bc_x);
-// True where no adjoint sweep needs the pack (the y and z sweeps, and the x sweep
-// unless it takes rows, recover for themselves).
-bool adjoint_small(const int n[3], int order, int elem);
+// True where the sweep along dir takes short tiles, which recover for themselves
+// (along x unless it takes rows).
+bool adjoint_small(int dir, const int n[3], int order, int elem);
+// True where a sweep of the adjoint reads the pack.
+bool adjoint_reads_pack(const int n[3], int bc_x, int order, int elem);
 template <class T>
 hipError_t launch_fill_zero(T* p, long long n, hipStream_t s);
 template <class T>
