@@ -70,8 +70,8 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
 }
 
 // Analytic Hubble-like flow at (x, y, z, t), converted to conserved variables.
-// With v = x/t the Lorentz factor is t/tau, so one reciprocal square root of
-// tau^2 = t^2 - r^2 gives s = t0/tau and g^2 = (t/tau)^2, and the only division
+// With v = x/t the Lorentz factor is |t|/tau, so one reciprocal square root of
+// tau^2 = t^2 - r^2 gives s = t0/tau and g = |t|/tau, and the only division
 // left is 1/t.  The ghost cells of a tile's edge are evaluated by a few lanes
 // while their wave waits, so the length of this chain is what counts: with two
 // roots and six divisions (each about 15 FP64 instructions) a 128^3 step took
@@ -81,7 +81,7 @@ __device__ inline void hubble_conserved(const HubbleBC& hb, double x, double y, 
                                         double u[5]) {
     const double t = hb.t;
     const double q = rsqrt_pos(t * t - (x * x + y * y + z * z));   // 1 / tau
-    const double s = hb.t0 * q, g = t * q;
+    const double s = hb.t0 * q, g = fabs(t) * q;
     const double s3 = s * s * s;
     const double p = hb.e0 * (s3 * s) * (1.0 / 3.0);
     const double w = 4.0 * p * (g * g);
