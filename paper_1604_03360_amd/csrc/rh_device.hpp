@@ -61,36 +61,37 @@ __device__ __forceinline__ double sqrt_pos(double x) {
     return fma(d, h, g);
 }
 
-// Reciprocal square root of a positive normal double: the hardware estimate y
-// with one third-order step, e = 1 - x y^2, y (1 + e/2 + 3 e^2/8).
-__device__ __forceinline__ double rsqrt_pos(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-(x * y), y, 1.0);
-    return fma(y * e, fma(0.375, e, 0.5), y);
-}
-
 // Analytic Hubble-like flow at (x, y, z, t), converted to conserved variables.
-// With v = x/t the Lorentz factor is |t|/tau, so one reciprocal square root of
-// tau^2 = t^2 - r^2 gives s = t0/tau and g = |t|/tau, and the only division
-// left is 1/t.  The ghost cells of a tile's edge are evaluated by a few lanes
-// while their wave waits, so the length of this chain is what counts: with two
-// roots and six divisions (each about 15 FP64 instructions) a 128^3 step took
-// 525 us in FP64 and 352 us in FP32, now 511 and 333 (24^3: 42.0 and 35.4, now
-// 40.8 and 33.6).
+// With v = x/t the Lorentz factor is |t|/tau, and only q = 1/tau^2 = 1/(t^2 - r^2) is
+// needed: (t0/tau)^2 = t0^2 q, gamma^2 = t^2 q.  The ghost cells of a tile's edge are
+// evaluated by a few lanes while their wave waits, so the length of this chain is what
+// counts, with its registers where the stage spills: no root and no other division
+// (128^3 step with two roots and six divisions 525 us in FP64 and 352 us in FP32, with one
+// reciprocal root in their place 511 and 333).  The energy holds q to the third power, so
+// the rounding of the last and largest sum in r^2 is taken off tau^2: the error of E is
+// 2.8e-16 rms and 1.3e-15 at most for |x|, |y|, |z| <= 5, t = 10 .. 11 (1.5e-15 at most
+// without it; the formulas as they are written, with roots and divisions, 3.6e-16 and
+// 1.4e-15; from one reciprocal root 4.7e-16 and 1.9e-15, at 458 us per 128^3 step of the
+// fused stage in FP64 and 276 us in FP32, now 447 and 273).  Taking off all of the rounding
+// spills 8 - 12 more registers there and costs 4 - 9% of the step.
 __device__ inline void hubble_conserved(const HubbleBC& hb, double x, double y, double z,
                                         double u[5]) {
     const double t = hb.t;
-    const double q = rsqrt_pos(t * t - (x * x + y * y + z * z));   // 1 / tau
-    const double s = hb.t0 * q, g = fabs(t) * q;
-    const double s3 = s * s * s;
-    const double p = hb.e0 * (s3 * s) * (1.0 / 3.0);
-    const double w = 4.0 * p * (g * g);
-    const double wt = w * fast_rcp(t);
-    u[0] = w - p;
-    u[1] = wt * x;
-    u[2] = wt * y;
-    u[3] = wt * z;
-    u[4] = hb.n0 * s3 * g;
+    const double b = fma(y, y, z * z), r2 = fma(x, x, b);
+    const double tau2 = fma(t, t, -r2) - fma(x, x, b - r2);
+    // reciprocal from the square of the hardware's reciprocal root (within 2^-23) and one
+    // third-order step; not a number outside the light cone, as the flow is there
+    const double y0 = __builtin_amdgcn_rsq(tau2), r0 = y0 * y0;
+    const double e = fma(-tau2, r0, 1.0);
+    const double q = fma(r0, fma(e, e, e), r0);
+    const double s2 = (hb.t0 * hb.t0) * q, g = t * q;
+    const double p = hb.e0 * (s2 * s2) * (1.0 / 3.0);
+    const double k = 4.0 * p * g;   // (e + p) gamma^2 / t
+    u[0] = k * t - p;
+    u[1] = k * x;
+    u[2] = k * y;
+    u[3] = k * z;
+    u[4] = hb.n0 * s2 * (hb.t0 * fabs(g));
 }
 
 // Closed-form primitive recovery for p = e/3 (FP64):

@@ -64,5 +64,19 @@ def test_ghosts_follow_the_formulas(t):
     assert np.all(np.abs(got - ref) <= 1e-14 * np.abs(ref))
 
 
+@pytest.mark.parametrize("t", [10.3, 8.1, -10.3])
+def test_ghosts_are_as_accurate_as_the_formulas(t):
+    """Their errors, rms and largest, are no larger than those of the formulas evaluated
+    in double precision with correctly rounded roots and divisions."""
+    ref = plain(t, np.longdouble)[0]
+    scale = np.where(ref == 0, 1, np.abs(ref))
+    got = np.abs(ghost_states(t) - ref) / scale
+    bar = np.abs(plain(t, np.float64)[0] - ref) / scale
+    rms = lambda e: np.sqrt((e * e).mean(axis=(1, 2, 3)))
+    print(rms(got), rms(bar), got.max(axis=(1, 2, 3)), bar.max(axis=(1, 2, 3)), flush=True)
+    assert np.all(rms(got) <= rms(bar))
+    assert np.all(got.max(axis=(1, 2, 3)) <= bar.max(axis=(1, 2, 3)))
+
+
 def test_ghosts_outside_the_light_cone_are_not_finite():
     assert not np.any(np.isfinite(boundary_L(1.0)))
