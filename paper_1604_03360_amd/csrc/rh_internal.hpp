@@ -66,7 +66,8 @@ struct AdjArgs {
     long long fstride;
     int n[3];
     int bc;             // boundary condition of the sweep axis
-    int seg;            // owned segment length along the axis
+    int seg;            // owned segment length along the axis (rolls)
+    unsigned row;       // blocks in a row of the launch (short tiles)
     T inv_h;
     T eps;
     T scale;            // ub += scale * (J^T w) of this axis
