@@ -1127,6 +1127,18 @@ rh_status batch_step_impl(rh_batch* b, double dt, int nsteps, double t) {
     return RH_OK;
 }
 
+// Default z segment of a batch's fused stage for its tile.
+int batch_default_segment(const rh_batch* b) {
+    std::vector<int> n(3 * (size_t)b->ngrid);
+    for (int i = 0; i < b->ngrid; ++i) {
+        n[3 * i] = b->d[i].nx;
+        n[3 * i + 1] = b->d[i].ny;
+        n[3 * i + 2] = b->d[i].nz;
+    }
+    return rh::stage_segment(b->ngrid, (const int (*)[3])n.data(), b->stage_tx, b->scheme, (int)b->elem,
+                             b->d[0].flux_split == RH_SPLIT_LOCAL);
+}
+
 rh_status check_batch(const rh_batch* b) {
     if (!b) return fail(RH_E_INVAL, "batch is NULL");
     if (!b->bound) return fail(RH_E_STATE, "batch has no bound state/workspace (call rh_batch_bind)");
@@ -1194,14 +1206,7 @@ rh_status rh_batch_create(rh_batch** out, int n_grids, const rh_grid_desc* descs
             b->tile_x = tx;
         }
     }
-    std::vector<int> n(3 * (size_t)n_grids);
-    for (int i = 0; i < n_grids; ++i) {
-        n[3 * i] = b->d[i].nx;
-        n[3 * i + 1] = b->d[i].ny;
-        n[3 * i + 2] = b->d[i].nz;
-    }
-    b->stage_seg = rh::stage_segment(n_grids, (const int (*)[3])n.data(), b->stage_tx, b->scheme, (int)b->elem,
-                                     b->d[0].flux_split == RH_SPLIT_LOCAL);
+    b->stage_seg = batch_default_segment(b);
     hipError_t e;
     if ((e = hipMalloc(&b->d_clamps, sizeof(unsigned))) != hipSuccess ||
         (e = hipMalloc(&b->d_partials, 6 * rh::kTotalsBlocks * sizeof(double))) != hipSuccess ||
@@ -1467,7 +1472,8 @@ rh_status rh_batch_autotune(rh_batch* b, int reps) {
         return RH_OK;
     };
     if (b->path != RH_PATH_SWEEPS) {
-        // fused stage: x-y tile width and z segment, timed on evaluations of L
+        // fused stage: x-y tile width and z segment (the default of each width and
+        // seven more), timed on evaluations of L
         // into the workspace's last state (the ideal gas's recovered fields, in
         // the first, computed once before the timed launches)
         auto time_stage = [&](float* ms) -> rh_status {
@@ -1518,16 +1524,16 @@ rh_status rh_batch_autotune(rh_batch* b, int reps) {
         rh_status rs = RH_OK;
         for (int tx : {16, 32}) {
             if (tx == 32 && b->scheme != 5) continue;
-            for (int sg : {4, 8, 16, 24, 32, 48, 64}) {
+            for (int sg : {0, 4, 8, 16, 24, 32, 48, 64}) {
                 b->stage_tx = tx;
-                b->stage_seg = sg;
+                b->stage_seg = sg > 0 ? sg : batch_default_segment(b);
                 if ((rs = upload_table(b)) != RH_OK) break;
                 float ms;
                 if ((rs = time_stage(&ms)) != RH_OK) break;
                 if (ms < bms) {
                     bms = ms;
                     btx = tx;
-                    bseg = sg;
+                    bseg = b->stage_seg;
                 }
             }
             if (rs != RH_OK) break;
