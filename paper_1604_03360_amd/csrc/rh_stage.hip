@@ -105,7 +105,12 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
 
     const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX;
     const bool act = lx < xa && ly < ya;
-    // lanes outside a ragged tile follow the loop on a valid cell and store nothing
+    // lanes outside a ragged tile follow the loop on a valid cell and store nothing; in
+    // FP32 WENO7 they leave the z window out, so that waves without a cell free the SIMD
+    // (ensemble of six 256x4x256 grids 1256 -> 1106 us per step, cubes the same).  The branch
+    // costs the other instances that fill their SIMDs (FP32 WENO5 128^3 265 -> 292).
+    constexpr bool kSkipZ = sizeof(T) == 4 && ORDER == 7 && !HUB;
+    const bool inz = !kSkipZ || act;
     const int cx = x0 + min(lx, xa - 1), cy = y0 + min(ly, ya - 1);
     const uint32_t sb = (uint32_t)sizeof(T) * (uint32_t)nx * (uint32_t)ny;   // z plane, bytes
     const uint32_t cb = (uint32_t)sizeof(T) * ((uint32_t)cx + (uint32_t)nx * (uint32_t)cy);
@@ -405,7 +410,7 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
 
     // z window of face k0 - 1/2: planes k0 - R .. k0 + R - 1, all loads issued
     // before the first recovery (a block of few planes waits once, not 2R times)
-    {
+    if (inz) {
         T fu[W][5];
 #pragma unroll
         for (int j = 0; j < W; ++j) fetch_own(k0 - R + j, fu[j]);
@@ -427,8 +432,10 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
     fetch_plane(k0, no5);
     fetch_halo(k0, nh5);
     T Fl[5];
+    if (inz) {
 #pragma unroll
-    for (int c = 0; c < 5; ++c) Fl[c] = zface(c);
+        for (int c = 0; c < 5; ++c) Fl[c] = zface(c);
+    }
 
     for (int k = k0; k < kend; ++k) {
         T uz[5], u[5];
@@ -443,7 +450,8 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
             fetch_plane(k + 1, no5);
             fetch_halo(k + 1, nh5);
         }
-        {
+        T Lz[5];
+        if (inz) {
             T fp[5], fm[5], sz = (T)0;
             z_pair(k + R, uz, fp, fm, sz);
 #pragma unroll
@@ -461,15 +469,14 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
                 for (int j = 0; j < W - 1; ++j) zsp[j] = zsp[j + 1];
                 zsp[W - 1] = sz;
             }
-        }
-        T Lz[5];
 #pragma unroll
-        for (int c = 0; c < 5; ++c) {
-            // the z face is reconstructed for every grid (on ghost copies where nz is
-            // 1) and discarded by a select, which keeps it out of a branch
-            const T Fr = zface(c);
-            Lz[c] = doz ? (Fl[c] - Fr) * hzinv : (T)0;
-            Fl[c] = Fr;
+            for (int c = 0; c < 5; ++c) {
+                // the z face is reconstructed for every grid (on ghost copies where nz is
+                // 1) and discarded by a select, which keeps it out of a branch
+                const T Fr = zface(c);
+                Lz[c] = doz ? (Fl[c] - Fr) * hzinv : (T)0;
+                Fl[c] = Fr;
+            }
         }
         const uint32_t off = cb + (uint32_t)k * sb;
         T u0k[5];
