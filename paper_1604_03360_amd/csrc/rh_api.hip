@@ -264,7 +264,7 @@ struct PathCost {
 };
 constexpr PathCost kPathCost[2][2] = {   // [WENO5, WENO7][FP32, FP64]
     {{5.6, 15.5, 165.0, 128.0, 98.0, 78.0}, {1.9, 17.2, 160.0, 255.0, 208.0, 102.0}},
-    {{9.5, 23.8, 229.0, 210.0, 198.0, 125.0}, {0.0, 22.4, 199.0, 305.0, 285.0, 169.0}},
+    {{9.5, 24.2, 229.0, 210.0, 198.0, 125.0}, {0.0, 22.4, 199.0, 305.0, 285.0, 169.0}},
 };
 
 bool auto_stage(const rh_grid_desc& d) {
