@@ -772,7 +772,7 @@ __global__ void __launch_bounds__(kSmallLanes, (AdjSmall<T, ORDER, HALF>::waves)
     const int nd = A.n[DIR];
     const int nlines = DIR == 0 ? A.n[1] * A.n[2] : DIR == 1 ? A.n[0] * A.n[2] : A.n[0] * A.n[1];
     const int ntx = (nd + TX - 1) / TX;
-    const unsigned blk = blockIdx.x + A.row * blockIdx.y;
+    const unsigned blk = blockIdx.x + (unsigned)A.seg * blockIdx.y;
     const int bx = (int)(blk % ntx), by = (int)(blk / ntx);
     const int x0 = bx * TX, r0 = by * TY;
     const int tid = threadIdx.x;
@@ -1265,8 +1265,8 @@ static void launch_adjoint_small(AdjArgs<T> a, const Lin3<T>& init, hipStream_t 
     // tile idle (no lane has a line).  Returning early there instead cost small grids a
     // second load of the arguments (12^3 FP32 WENO5: 11.4 against 12.0 us).
     const long long nblk = ntx * nrt, rows = (nblk + (1 << 22) - 1) >> 22;
-    a.row = (unsigned)((nblk + rows - 1) / rows);
-    const dim3 grid(a.row, (unsigned)rows);
+    a.seg = (int)((nblk + rows - 1) / rows);
+    const dim3 grid((unsigned)a.seg, (unsigned)rows);
     if constexpr (sizeof(T) == 8 && ORDER == 7) {
         if (nblk > 512) {
             adj_small<T, ORDER, DIR, true><<<grid, kSmallLanes, 0, s>>>(a, init);

@@ -66,8 +66,9 @@ struct AdjArgs {
     long long fstride;
     int n[3];
     int bc;             // boundary condition of the sweep axis
-    int seg;            // owned segment length along the axis (rolls)
-    unsigned row;       // blocks in a row of the launch (short tiles)
+    int seg;            // rolls: owned segment length along the axis; short tiles: blocks in a
+                        // row of the launch (one field: another one moved the rest of the
+                        // arguments to a further load, 1% of the FP32 rolls)
     T inv_h;
     T eps;
     T scale;            // ub += scale * (J^T w) of this axis
