@@ -255,7 +255,9 @@ rh_status rh_set_graph(rh_plan* plan, int enable);
  * local splitting or the ideal gas). */
 rh_status rh_set_path(rh_plan* plan, int path);
 
-/* The path the plan's evaluations take now (RH_PATH_SWEEPS or RH_PATH_STAGE). */
+/* The path the plan's evaluations of L take now (RH_PATH_SWEEPS or RH_PATH_STAGE; on
+ * RH_PATH_AUTO it can change with rh_set_timing).  rh_step of a one-dimensional grid
+ * on RH_PATH_AUTO takes neither (see RH_PATH_AUTO). */
 rh_status rh_get_path(const rh_plan* plan, int* path);
 
 /* Launch shape of the fused stage: tile_x (16, or 32 for WENO5) cells along x by 256/tile_x
@@ -292,7 +294,10 @@ rh_status rh_totals_noalloc(const void* state, int precision, long long ncell, d
 rh_status rh_reset_counters(rh_plan* plan);
 
 /* Enable (nonzero) or disable per-kernel timing with HIP events recorded on
- * the bound stream around every launch.  Enabling clears earlier records. */
+ * the bound stream around every launch.  Enabling clears earlier records.  On
+ * RH_PATH_AUTO timed evaluations take the directional sweeps where the scheme has
+ * them, with the same results, while untimed ones may take the fused stage or (lines)
+ * several steps per launch: to time the fused stage set RH_PATH_STAGE. */
 rh_status rh_set_timing(rh_plan* plan, int enable);
 
 /* Per kernel class (RH_KERNEL_*): total milliseconds and number of launches

@@ -1,16 +1,17 @@
 // rh_adjoint.hip -- gfx950 kernels of the adjoint of L and of the SSP-RK3 step.
 //
-// One adjoint sweep per axis, all reading a per-cell pack of the primitive
-// recovery and its derivatives (FP64 arithmetic).  The x sweep stages
+// One adjoint sweep per axis, from the primitive recovery of each cell and its
+// derivatives (FP64 arithmetic, in a per-cell pack).  The x sweep stages
 // contiguous cells in LDS, differentiates each face once and gathers the face
 // partials per cell; it writes the output from the caller's linear combination
 // plus its part.  On periodic rows of 32..256 cells it takes whole rows
 // (adj_xrow) and also computes and stores the pack; otherwise it takes short tiles
 // that recover for themselves (adj_small) or, in FP32 WENO5 on large grids, longer
-// ones that read the pack (adj_x); a launch of its own (adj_pack) then fills the
-// pack.  Small grids take adj_small along every axis and need no pack.  The y and
-// z sweeps of large grids (adj_roll) give each lane a segment [k0, k1) of one grid line; the lane rolls along it
-// over every face whose stencil reaches an owned position (the segment plus R
+// ones that read the pack (adj_x).  Along y and z small grids take adj_small as well
+// (adjoint_small), large ones and short axes a rolling sweep that reads the pack
+// (adj_roll); where a sweep reads it and no row kernel has, a launch of its own fills it
+// (adj_pack).  adj_roll gives each lane a segment [k0, k1) of one grid line; the lane rolls
+// along it over every face whose stencil reaches an owned position (the segment plus R
 // faces on each side), keeping a register window of 2R cells of split fluxes
 // and of split-flux adjoints; for each face it adds the face weight
 // g = (w_{i+1} - w_i)/h times the WENO gradients to the window, and a position

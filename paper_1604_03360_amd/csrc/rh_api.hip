@@ -2,9 +2,10 @@
 //
 // A plan describes one grid; the caller owns the state and workspace buffers
 // and the stream.  rh_step enqueues, per SSP-RK3 stage (Sec. 1 of Sikorski et
-// al., arXiv:1604.03360), one directional sweep per axis longer than one cell,
-// in the order x, y, z; the first sweep starts the L accumulator and the last
-// one fuses the stage combine.
+// al., arXiv:1604.03360), one launch of the fused stage, or one directional sweep per
+// axis longer than one cell, in the order x, y, z (the first sweep starts the L
+// accumulator and the last one fuses the stage combine); one-dimensional grids
+// advance several steps per launch.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -113,8 +113,8 @@ __device__ __forceinline__ void recover_closed(double E, double E2, double M2, d
 // fewer exec-mask updates than a branch for each kind around the closed form, and the
 // same bits.  Per step, branches around -> one branch after, us: MUSTA-FORCE 128^3
 // FP64 507 -> 488, FP32 392 -> 372, 24^3 33.4 -> 30.6; WENO5 192^3 FP64 1496 -> 1478.
-// TIGHT keeps the branches around it, which hold fewer registers: the fused stage
-// with analytic ghosts spills otherwise (192^3 FP64 1571 us, 1619 with one branch).
+// TIGHT keeps the branches around it, which hold fewer registers: the fused FP64 stage
+// with analytic ghosts spills more otherwise (128^3 WENO5 448 us, 452 with one branch).
 template <bool TIGHT = false>
 __device__ __forceinline__ void recover_kp3(double E, double Mx, double My, double Mz, double& kap,
                                             double& Mxs, double& Mys, double& Mzs, double& p,

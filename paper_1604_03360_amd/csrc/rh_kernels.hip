@@ -638,8 +638,7 @@ static hipError_t launch_roll(SweepArgs<T> a, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Fused x and y sweeps (periodic x, nx a multiple of 64 up to 256; WENO5, and
-// WENO7 in FP32)
+// Fused x and y sweeps (periodic x of 256 cells; FP32 WENO5 also 64, 128 and 192)
 // ---------------------------------------------------------------------------
 // A block holds whole x rows (lane = x) of one z plane and rolls along a y
 // segment like sweep_roll_body.  Each row that enters the y window is
