@@ -239,12 +239,15 @@ bool needs_recovery(const rh_grid_desc& d) { return d.eos == RH_EOS_IDEAL && d.s
 // One launch per stage instead of three wins wherever latency or the L accumulator's
 // traffic counts, unless its tiles stay empty: a tile is 16 x 16, so an axis of a few
 // cells along x or y leaves most of its lanes idle, where the sweeps only pad x.
-// The stage's estimate is linear in the planes of its segment model.  The sweeps' joins
-// a latency and a throughput (us per cell, less where the fused x-y sweep takes rows of
-// 256, and per cell that pads x to 16) as the 1.5-norm.  Fitted to both paths timed at 170
-// random and 70 chosen shapes of 2 .. 4096 cells an axis, weighted to where they are close:
-// the choice costs 0.1 - 0.3% on average against the faster path, and more than 3% at
-// one shape in 30.
+// The stage's estimate is linear in the planes of its segment model; that of the sweeps
+// sums what its launches take: the rolling sweeps by the faces of a lane and the rounds of
+// blocks (blocks per CU slow each other to q; between whole rounds and none idle), the x
+// sweep by padded cells and tiles, and the accumulator traffic past the 256 MB cache.
+// Fitted to both paths timed at 230 random and chosen shapes of 2 .. 4096 cells an
+// axis and 680 where size alone chooses otherwise, weighted to where they are close; in
+// WENO5 the stage's estimate is 3 - 5% below its fit, which trades a late change
+// for an early one.  The choice costs 0.05 - 0.15% on average against the faster path,
+// and more than 3% at one shape in 60.
 // Sweeps and stage, us per step:
 //                  FP32 WENO5    FP64 WENO5    FP32 WENO7    FP64 WENO7
 //   33x20x17        135    31
@@ -260,25 +263,51 @@ bool needs_recovery(const rh_grid_desc& d) { return d.eos == RH_EOS_IDEAL && d.s
 //   256x8x256       192   140     204   216     276   261     267   373
 //   1024x1024x4     609   499    1169   916     974  1012    1505  1743
 struct PathCost {
-    double stage, plane;                    // stage: us fixed, and per plane of the segment model
-    double sweeps, cell, row_cell, x_pad;   // sweeps: us of latency, per 10^6 cells, the same in rows of 256, per 10^6 padding cells
+    double stage, plane;   // stage: us fixed, per plane of the segment model
+    double sweeps;         // sweeps: us fixed,
+    double face;           // per face of a rolling lane and round,
+    double cell, tile;     // x sweep: per 10^6 padded cells, per 10^6 rows of a tile,
+    double row_face;       // fused x-y sweep: per face and round,
+    double uncached;       // per 10^6 cells past the cache
+    double q, whole;       // share of its lone time a block takes among occ; weight of whole rounds
 };
 constexpr PathCost kPathCost[2][2] = {   // [WENO5, WENO7][FP32, FP64]
-    {{5.6, 15.5, 165.0, 128.0, 98.0, 78.0}, {1.9, 17.2, 160.0, 255.0, 208.0, 102.0}},
-    {{9.5, 24.2, 229.0, 210.0, 198.0, 125.0}, {0.0, 22.4, 199.0, 305.0, 285.0, 169.0}},
+    {{4.5, 15.1, 69.9, 2.62, 44.1, 328.0, 5.1, 20.2, 0.6, 0.25}, {0.0, 16.5, 16.8, 4.98, 49.1, 311.0, 6.5, 25.7, 0.9, 0.25}},
+    {{12.9, 24.2, 132.0, 2.03, 93.0, 232.0, 6.21, 28.8, 0.9, 0.75}, {0.0, 22.4, 45.8, 4.1, 128.0, 283.0, 9.57, 29.2, 0.9, 0.5}},
 };
+
+// Time of `blocks` blocks of a rolling sweep, in faces of one that has its CU to itself;
+// occ blocks share a CU.
+double roll_rounds(const PathCost& c, long long blocks, int occ, double faces) {
+    const long long per_cu = (blocks + 255) / 256, rest = per_cu % occ;
+    const double all = occ * c.q * faces, busy = blocks * c.q * faces / 256.0;
+    double t = (per_cu / occ) * all;
+    if (rest) t += faces * (1.0 + (occ * c.q - 1.0) * (rest - 1) / (occ - 1));
+    return c.whole * t + (1.0 - c.whole) * (busy > faces ? busy : faces);
+}
 
 bool auto_stage(const rh_grid_desc& d) {
     if (d.nx < 2 || d.ny < 2 || d.nz < 2 || needs_stage(d)) return false;
     const int n[3] = {d.nx, d.ny, d.nz};
-    const int elem = d.precision == RH_PREC_FP32 ? 4 : 8;
+    const int elem = d.precision == RH_PREC_FP32 ? 4 : 8, occ = elem == 4 ? 3 : 2;
     const PathCost& c = kPathCost[d.scheme == 7][elem == 8];
     double planes;
     rh::stage_segment(1, &n, 16, d.scheme, elem, false, &planes);
-    const double yz = 1e-6 * d.ny * d.nz;
-    const bool rows = d.nx == 256 && rh::sweep_xy_applies(d.scheme, elem, n, d.bc[0]);
-    const double busy = yz * ((rows ? c.row_cell : c.cell) * d.nx + c.x_pad * ((16 - d.nx % 16) % 16));
-    const double sweeps = std::pow(std::pow(c.sweeps, 1.5) + std::pow(busy, 1.5), 1.0 / 1.5);
+    auto roll = [&](int nd, long long lanes) {
+        const long long gx = (lanes + 255) / 256;
+        const int seg = rh::choose_segment(nd, (int)(gx * 256));
+        return c.face * roll_rounds(c, gx * ((nd + seg - 1) / seg), occ, seg + d.scheme);
+    };
+    double sweeps = c.sweeps + roll(d.nz, (long long)d.nx * d.ny);
+    if (d.nx == 256 && rh::sweep_xy_applies(d.scheme, elem, n, d.bc[0])) {
+        const int seg = rh::choose_segment(d.ny, d.nx * d.nz);
+        sweeps += c.row_face * roll_rounds(c, (long long)d.nz * ((d.ny + seg - 1) / seg), occ, seg + d.scheme);
+    } else {
+        const int tx = rh::choose_tile_x(d.nx, (d.scheme + 1) / 2);
+        const double tiles = 1e-6 * ((d.nx + tx - 1) / tx) * d.ny * d.nz;
+        const double over = 1e-6 * d.nx * d.ny * d.nz - (elem == 4 ? 3.2 : 1.6);
+        sweeps += roll(d.ny, (long long)d.nx * d.nz) + (c.cell * tx + c.tile) * tiles + (over > 0.0 ? c.uncached * over : 0.0);
+    }
     return c.stage + c.plane * planes < sweeps;
 }
 
