@@ -103,6 +103,7 @@ struct rh_plan {
     int stage_seg = 0;           // 0: default segment for the grid
     int default_seg = 1;         // that default, for stage_tx
     bool auto_stage = false;     // RH_PATH_AUTO takes the fused stage
+    bool sparse = false;         // its tiles are mostly empty
     // one captured step, replayed by rh_step when enabled
     bool graph_on = false;
     hipStream_t cap_stream = nullptr;
@@ -224,10 +225,10 @@ bool adjoint_supported(const rh_grid_desc& d) { return !needs_stage(d); }
 
 // Launch one fused-stage evaluation of the scheme of d over nblocks blocks.
 template <class T>
-hipError_t launch_stage_of(const rh_grid_desc& d, int tx, bool hub, const rh::StageArgs<T>& sa,
+hipError_t launch_stage_of(const rh_grid_desc& d, int tx, bool hub, bool sparse, const rh::StageArgs<T>& sa,
                            long long nblocks, hipStream_t s) {
     if (d.scheme == RH_SCHEME_MUSTA) return rh::launch_musta<T>(hub, d.eos, d.limiter, d.musta_stages, sa, nblocks, s);
-    return rh::launch_stage<T>(d.scheme, tx, hub, d.flux_split == RH_SPLIT_LOCAL, d.eos, sa, nblocks, s);
+    return rh::launch_stage<T>(d.scheme, tx, hub, d.flux_split == RH_SPLIT_LOCAL, d.eos, sparse, sa, nblocks, s);
 }
 
 // The ideal-gas WENO stage reads every cell's velocity, pressure and sound
@@ -375,7 +376,7 @@ rh_status evaluate(rh_plan* p, const T* us, const T* u0, T* lacc, T* uout, doubl
             if (st != RH_OK) return st;
         }
         return timed_launch(p, RH_KERNEL_STAGE, [&] {
-            return launch_stage_of<T>(p->d, p->stage_tx, any_hubble(p), sa, nb, p->stream);
+            return launch_stage_of<T>(p->d, p->stage_tx, any_hubble(p), p->sparse, sa, nb, p->stream);
         }, "stage launch");
     }
     int i0 = 0;
@@ -653,6 +654,7 @@ rh_status rh_plan_create(rh_plan** out, const rh_grid_desc* d) {
     p->ncell = (long long)n[0] * n[1] * n[2];
     p->elem = d->precision == RH_PREC_FP32 ? 4 : 8;
     p->auto_stage = auto_stage(p->d);
+    p->sparse = rh::stage_sparse(1, &n);
     set_default_segment(p);
     hipError_t e;
     if ((e = hipMalloc(&p->d_clamps, sizeof(unsigned))) != hipSuccess ||
@@ -910,6 +912,7 @@ struct rh_batch {
     int nblocks[3] = {0, 0, 0};
     void* d_grids = nullptr;         // BatchGrid<T>[ngrid]
     int stage_tx = 16, stage_seg = 32;       // fused stage
+    bool sparse = false;                     // its tiles are mostly empty
     long long stage_nblocks = 0;
     long long recover_nblocks = 0;   // ideal-gas recovery pass over every grid
     void* d_stage = nullptr;         // StageGrid<T>[ngrid]
@@ -1064,7 +1067,7 @@ rh_status batch_evaluate(rh_batch* b, hipStream_t s, const T* us, const T* u0, T
             if (st != RH_OK) return st;
         }
         return batch_timed(b, s, RH_KERNEL_STAGE, [&] {
-            return launch_stage_of<T>(b->d[0], b->stage_tx, b->any_hubble, sa, b->stage_nblocks, s);
+            return launch_stage_of<T>(b->d[0], b->stage_tx, b->any_hubble, b->sparse, sa, b->stage_nblocks, s);
         }, "batched stage launch");
     }
     rh::BatchArgs<T> B;
@@ -1157,14 +1160,20 @@ rh_status batch_step_impl(rh_batch* b, double dt, int nsteps, double t) {
     return RH_OK;
 }
 
-// Default z segment of a batch's fused stage for its tile.
-int batch_default_segment(const rh_batch* b) {
+// Cells of a batch's grids, three per grid.
+std::vector<int> batch_cells(const rh_batch* b) {
     std::vector<int> n(3 * (size_t)b->ngrid);
     for (int i = 0; i < b->ngrid; ++i) {
         n[3 * i] = b->d[i].nx;
         n[3 * i + 1] = b->d[i].ny;
         n[3 * i + 2] = b->d[i].nz;
     }
+    return n;
+}
+
+// Default z segment of a batch's fused stage for its tile.
+int batch_default_segment(const rh_batch* b) {
+    const std::vector<int> n = batch_cells(b);
     return rh::stage_segment(b->ngrid, (const int (*)[3])n.data(), b->stage_tx, b->scheme, (int)b->elem,
                              b->d[0].flux_split == RH_SPLIT_LOCAL);
 }
@@ -1237,6 +1246,7 @@ rh_status rh_batch_create(rh_batch** out, int n_grids, const rh_grid_desc* descs
         }
     }
     b->stage_seg = batch_default_segment(b);
+    b->sparse = rh::stage_sparse(n_grids, (const int (*)[3])batch_cells(b).data());
     hipError_t e;
     if ((e = hipMalloc(&b->d_clamps, sizeof(unsigned))) != hipSuccess ||
         (e = hipMalloc(&b->d_partials, 6 * rh::kTotalsBlocks * sizeof(double))) != hipSuccess ||
@@ -1521,7 +1531,7 @@ rh_status rh_batch_autotune(rh_batch* b, int reps) {
                     sa.grids = (const rh::StageGrid<float>*)b->d_stage;
                     sa.ngrid = b->ngrid;
                     if (recover) er = rh::launch_recover_ideal<float>(sa, b->recover_nblocks, b->stream);
-                    else er = launch_stage_of<float>(b->d[0], b->stage_tx, b->any_hubble, sa, b->stage_nblocks, b->stream);
+                    else er = launch_stage_of<float>(b->d[0], b->stage_tx, b->any_hubble, b->sparse, sa, b->stage_nblocks, b->stream);
                 } else {
                     rh::StageArgs<double> sa;
                     std::memset(&sa, 0, sizeof(sa));
@@ -1534,7 +1544,7 @@ rh_status rh_batch_autotune(rh_batch* b, int reps) {
                     sa.grids = (const rh::StageGrid<double>*)b->d_stage;
                     sa.ngrid = b->ngrid;
                     if (recover) er = rh::launch_recover_ideal<double>(sa, b->recover_nblocks, b->stream);
-                    else er = launch_stage_of<double>(b->d[0], b->stage_tx, b->any_hubble, sa, b->stage_nblocks, b->stream);
+                    else er = launch_stage_of<double>(b->d[0], b->stage_tx, b->any_hubble, b->sparse, sa, b->stage_nblocks, b->stream);
                 }
                 return er == hipSuccess ? RH_OK : hip_fail(er, "autotune launch");
             };

@@ -207,10 +207,13 @@ long long stage_blocks(const StageGrid<T>& g) {
 }
 // Launch the fused stage over nblocks blocks (tile width tx in {16, 32}); hub
 // selects the instantiation with analytic (HUBBLE) ghost cells, local the
-// Lax-Friedrichs splitting with alpha per interface, eos the equation of state.
+// Lax-Friedrichs splitting with alpha per interface, eos the equation of state,
+// sparse the instance for mostly empty tiles (where there is one).
 template <class T>
-hipError_t launch_stage(int order, int tx, bool hub, bool local, int eos, const StageArgs<T>& a,
+hipError_t launch_stage(int order, int tx, bool hub, bool local, int eos, bool sparse, const StageArgs<T>& a,
                         long long nblocks, hipStream_t s);
+// True where the grids fill a quarter of the lanes of their 16 x 16 tiles or less.
+bool stage_sparse(int ngrid, const int (*n)[3]);
 // z segment of the stage kernels for a launch over ngrid grids of n[g] cells
 // (scheme 5, 7 or RH_SCHEME_MUSTA; tiles of tx, elem bytes per value), and its
 // estimated time in planes of a block that has its CU to itself.

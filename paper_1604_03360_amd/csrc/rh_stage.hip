@@ -70,7 +70,11 @@ __device__ __forceinline__ void stage_pair(const T u[5], T v, T P, T a[5], T b[5
     }
 }
 
-template <class T, int ORDER, int TX, bool HUB, bool LOCAL, int EOS>
+// SPARSE: for grids that fill a quarter of their tiles or less.  Waves without a cell then
+// free their SIMD instead of following the z window (FP32 WENO7 ensemble of six 256x4x256
+// grids 1256 -> 1106 us per step); on full tiles the branch keeps the loads of the next plane
+// from overlapping it (33^3 62 -> 72, FP32 WENO5 128^3 265 -> 292).
+template <class T, int ORDER, int TX, bool HUB, bool LOCAL, int EOS, bool SPARSE = false>
 __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>::value)) stage_fused(StageArgs<T> A) {
     constexpr int R = (ORDER + 1) / 2, W = 2 * R, TY = 256 / TX;
     static_assert(W * (TX + TY) <= 256, "one halo cell per lane and plane");
@@ -105,12 +109,9 @@ __global__ void __launch_bounds__(256, (StageMinBlocks<T, ORDER, TX, HUB, LOCAL>
 
     const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX;
     const bool act = lx < xa && ly < ya;
-    // lanes outside a ragged tile follow the loop on a valid cell and store nothing; in
-    // FP32 WENO7 they leave the z window out, so that waves without a cell free the SIMD
-    // (ensemble of six 256x4x256 grids 1256 -> 1106 us per step, cubes the same).  The branch
-    // costs the other instances that fill their SIMDs (FP32 WENO5 128^3 265 -> 292).
-    constexpr bool kSkipZ = sizeof(T) == 4 && ORDER == 7 && !HUB;
-    const bool inz = !kSkipZ || act;
+    // lanes outside a ragged tile follow the loop on a valid cell and store nothing; with
+    // SPARSE they leave the z window out
+    const bool inz = !SPARSE || act;
     const int cx = x0 + min(lx, xa - 1), cy = y0 + min(ly, ya - 1);
     const uint32_t sb = (uint32_t)sizeof(T) * (uint32_t)nx * (uint32_t)ny;   // z plane, bytes
     const uint32_t cb = (uint32_t)sizeof(T) * ((uint32_t)cx + (uint32_t)nx * (uint32_t)cy);
@@ -601,6 +602,15 @@ int stage_segment(int ngrid, const int (*n)[3], int tx, int scheme, int elem, bo
     return best;
 }
 
+bool stage_sparse(int ngrid, const int (*n)[3]) {
+    long long cells = 0, lanes = 0;
+    for (int g = 0; g < ngrid; ++g) {
+        cells += (long long)n[g][0] * n[g][1] * n[g][2];
+        lanes += 256LL * ((n[g][0] + 15) / 16) * ((n[g][1] + 15) / 16) * n[g][2];
+    }
+    return lanes >= 4 * cells;
+}
+
 template <class T>
 void stage_shape(StageGrid<T>& g, int tx, int seg) {
     const int ty = 256 / tx;
@@ -613,8 +623,16 @@ void stage_shape(StageGrid<T>& g, int tx, int seg) {
 }
 
 template <class T, int ORDER, int TX>
-static hipError_t launch_stage_t(bool hub, bool local, int eos, const StageArgs<T>& a, dim3 grid, hipStream_t s) {
+static hipError_t launch_stage_t(bool hub, bool local, int eos, bool sparse, const StageArgs<T>& a, dim3 grid,
+                                 hipStream_t s) {
     if (eos == EOS_CONFORMAL) {
+        if constexpr (sizeof(T) == 4 && ORDER == 7) {
+            // the other instances gain too little there for a second one
+            if (sparse && !hub && !local) {
+                stage_fused<T, ORDER, TX, false, false, EOS_CONFORMAL, true><<<grid, 256, 0, s>>>(a);
+                return hipSuccess;
+            }
+        }
         if (hub && local) stage_fused<T, ORDER, TX, true, true, EOS_CONFORMAL><<<grid, 256, 0, s>>>(a);
         else if (hub) stage_fused<T, ORDER, TX, true, false, EOS_CONFORMAL><<<grid, 256, 0, s>>>(a);
         else if (local) stage_fused<T, ORDER, TX, false, true, EOS_CONFORMAL><<<grid, 256, 0, s>>>(a);
@@ -630,18 +648,18 @@ static hipError_t launch_stage_t(bool hub, bool local, int eos, const StageArgs<
 }
 
 template <class T>
-hipError_t launch_stage(int order, int tx, bool hub, bool local, int eos, const StageArgs<T>& a,
+hipError_t launch_stage(int order, int tx, bool hub, bool local, int eos, bool sparse, const StageArgs<T>& a,
                         long long nblocks, hipStream_t s) {
     if (nblocks <= 0 || nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nblocks);
     hipError_t e;
     if (order == 5) {
-        if (tx == 16) e = launch_stage_t<T, 5, 16>(hub, local, eos, a, grid, s);
-        else if (tx == 32) e = launch_stage_t<T, 5, 32>(hub, local, eos, a, grid, s);
+        if (tx == 16) e = launch_stage_t<T, 5, 16>(hub, local, eos, sparse, a, grid, s);
+        else if (tx == 32) e = launch_stage_t<T, 5, 32>(hub, local, eos, sparse, a, grid, s);
         else return hipErrorInvalidValue;
     } else if (order == 7) {
         // WENO7 tiles are 16 x 16 (a 32 x 8 tile has 320 halo cells per plane)
-        if (tx == 16) e = launch_stage_t<T, 7, 16>(hub, local, eos, a, grid, s);
+        if (tx == 16) e = launch_stage_t<T, 7, 16>(hub, local, eos, sparse, a, grid, s);
         else return hipErrorInvalidValue;
     } else {
         return hipErrorInvalidValue;
@@ -651,7 +669,7 @@ hipError_t launch_stage(int order, int tx, bool hub, bool local, int eos, const 
 
 template void stage_shape<float>(StageGrid<float>&, int, int);
 template void stage_shape<double>(StageGrid<double>&, int, int);
-template hipError_t launch_stage<float>(int, int, bool, bool, int, const StageArgs<float>&, long long, hipStream_t);
-template hipError_t launch_stage<double>(int, int, bool, bool, int, const StageArgs<double>&, long long, hipStream_t);
+template hipError_t launch_stage<float>(int, int, bool, bool, int, bool, const StageArgs<float>&, long long, hipStream_t);
+template hipError_t launch_stage<double>(int, int, bool, bool, int, bool, const StageArgs<double>&, long long, hipStream_t);
 
 }  // namespace rh
