@@ -111,7 +111,7 @@ __device__ __forceinline__ void weno5_grad_acc_e(T s0, T s1, T s2, T s3, T s4, T
 //   c_k = -2 omega_k (dq_k - sum_m omega_m dq_m) / G_k,
 // where the shared part q(D3, D2) of G_0 and G_1 takes c_0 + c_1 at once.  The
 // weights are 1/G_k^2 with one reciprocal per indicator, which c_k needs as well,
-// scaled to d_k / (beta_k + eps)^2: their sum overflows in FP32 where eps is below 1.4e-20
+// in FP32 scaled to d_k / (beta_k + eps)^2: their sum overflows where eps is below 1.4e-20
 // and the data flat (unscaled already below 1.8e-19; the forward evaluates down to 2.4e-22).
 // With tables of the derivatives of every candidate and indicator by every
 // stencil value (zeros multiplied too) J^T w took 1099 us at 128^3 FP64 and 636 us
@@ -128,7 +128,7 @@ __device__ __forceinline__ void weno7_grad_acc(const T s[7], T eps, T gbar, T o[
     const T dq2 = (T)(1.0 / 12.0) * (D3 - D5) + (T)0.5 * D4;
     const T dq3 = (T)0.75 * D4 - (T)(1.0 / 3.0) * D5 + (T)(1.0 / 12.0) * D6;
     const T r0 = fast_rcp(S.g0), r1 = fast_rcp(S.g1), r2 = fast_rcp(S.g2), r3 = fast_rcp(S.g3);
-    constexpr double d = f * f / 35.0;
+    constexpr double d = sizeof(T) == 4 ? f * f / 35.0 : 1.0;
     const T a0 = ((T)d * r0) * r0, a1 = ((T)(12.0 * d) * r1) * r1;
     const T a2 = ((T)(18.0 * d) * r2) * r2, a3 = ((T)(4.0 * d) * r3) * r3;
     const T rs = fast_rcp((a0 + a1) + (a2 + a3));
